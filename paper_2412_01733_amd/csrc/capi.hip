@@ -441,7 +441,11 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
         t->diag_pending = false;
         return TC_OK;
     }
-    const int64_t waves = walk_waves(n);
+    // Lists are kept only while they fit the budget; otherwise the adjoint re-walks.
+    const bool store = (flags & TC_STORE_LISTS) != 0 &&
+                       (uint64_t)walk_waves(n) * kListCap * sizeof(uint4) <= kListMaxBytes;
+    const int targets = t->counted || store ? 64 : walk_targets(n, mode);
+    const int64_t waves = (n + targets - 1) / targets;
     TC_TRY(ensure(t, t->diag_part, (size_t)waves * 4 * sizeof(double), s));
     TC_TRY(ensure(t, t->diag_temp, diag_temp_bytes(waves), s));
     if (t->counted) TC_TRY(ensure(t, t->sorted_counts, (size_t)n * 4, s));
@@ -454,9 +458,6 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
     a.diag = P<double>(t->diag_part);
     a.status = t->status;
     a.visits = t->visits;
-    // Lists are kept only while they fit the budget; otherwise the adjoint re-walks.
-    const bool store = (flags & TC_STORE_LISTS) != 0 &&
-                       (uint64_t)waves * kListCap * sizeof(uint4) <= kListMaxBytes;
     if (store) {
         TC_TRY(ensure(t, t->lists, (size_t)waves * kListCap * sizeof(uint4), s));
         TC_TRY(ensure(t, t->list_len, (size_t)waves * sizeof(uint32_t), s));
@@ -467,7 +468,8 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
 
     if (t->counted) launch_fill_u32((uint32_t*)t->visits, 2 * kNumVisitCounters, 0u, s);
     stage_begin(t, kStWalk, s);
-    launch_walk(a, mode, t->counted, store, s);
+    if (targets < 64) launch_walk_split(a, targets, mode, s);
+    else launch_walk(a, mode, t->counted, store, s);
     stage_end(t, kStWalk, s);
     TC_TRY(check_launch("walk"));
     stage_begin(t, kStDiag, s);
@@ -513,7 +515,9 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     stage_begin(t, kStBwdWalk, s);
     launch_fill_f64_zero(a.node_grad, nn * 4, s);
     launch_fill_f64_zero(a.part_grad, n * 4, s);
-    launch_walk_adjoint(a, t->last_mode, s);
+    const int targets = t->lists_stored ? 64 : adjoint_targets(n, t->last_mode);
+    if (targets < 64) launch_walk_split_adjoint(a, targets, t->last_mode, s);
+    else launch_walk_adjoint(a, t->last_mode, s);
     stage_end(t, kStBwdWalk, s);
     TC_TRY(check_launch("adjoint walk"));
     HIP_TRY(hipMemcpyAsync(&t->host->status, t->status, 4, hipMemcpyDeviceToHost, s));

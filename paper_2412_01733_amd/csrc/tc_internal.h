@@ -159,6 +159,13 @@ int64_t walk_waves(int64_t n);
 void launch_walk(const WalkArgs& a, tc_walk mode, bool count, bool store, hipStream_t s);
 void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 
+// walk_split.hip: the same walks with `targets` (8 or 16) targets a wavefront;
+// walk_targets / adjoint_targets: which to use for n particles (64: walk.hip)
+int walk_targets(int64_t n, tc_walk mode);
+int adjoint_targets(int64_t n, tc_walk mode);
+void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
+void launch_walk_split_adjoint(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
+
 // order.hip: the walk's target order (Hilbert order of the particles), from
 // the breadth-first topology records {first, count, child, meta} (written
 // densely by the upward pass) top-down; nord is node-sized scratch.

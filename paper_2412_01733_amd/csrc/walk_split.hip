@@ -1,0 +1,414 @@
+// The walk for few particles: a wavefront serves T = 8 or 16 targets.
+//
+// A wavefront that serves 64 targets (walk.hip) evaluates one node at a time for
+// all of them.  Below ~1e5 particles there are fewer such wavefronts than the
+// chip has places for, and each is a long serial chain: a lone wavefront issues
+// an instruction every ~8 cycles, whatever its dependences.  Here lane
+// s T + t handles target t and node slot s, so that S = 64 / T nodes are
+// evaluated at once, there are 64 / T times more wavefronts, and each has a
+// correspondingly shorter chain (the T targets lie closer together, so they also
+// open fewer nodes between them).  The price is that a node record is staged for
+// T targets instead of 64, which is why large inputs stay with walk.hip.
+//
+// A step takes up to 8 sibling groups off the stack and stages their <= 64
+// children, one per lane.  The box test of walk.hip sorts the children into
+// accepted by every target (list A, compacted in LDS), opened by every target of
+// the group's mask, and undecided (list M).  The slots take the entries of A in
+// one straight run; those of M with the per-target rule, which leaves each
+// entry's mask of opening targets in LDS.  Then all opened children push their
+// groups at once, each at the place that a prefix count gives it.
+//
+// Decisions are those of walk.hip, bit for bit: the FP32 offsets come from the
+// same anchor (the first target of the aligned 64), through the same operations.
+// Only the order of the sums differs; the slots' partial sums are added in FP64.
+#include <type_traits>
+
+#include "walk_common.h"
+
+namespace tc {
+namespace {
+
+constexpr int kSplitWaves = 4;
+constexpr int kSplitThreads = 64 * kSplitWaves;
+// Stack bound.  An entry at position p whose nodes lie at level l is safe if
+//   p + 1 + 7 + 7 (20 - l) + 1 <= kSplitStack:
+// a depth-first descent from it grows the stack by at most 7 a level.  Group j
+// of a step (j = 0 the top) pushes at positions below sp - ng + 8 (j + 1), so it
+// joins the step only while sp + 7 (j + 1) + 7 (20 - l) + 1 <= kSplitStack, which
+// makes its children's groups safe in turn; the top group always satisfies this,
+// by being safe, and the first entry does (142).
+constexpr int kSplitStack = 256;
+static_assert(kSplitStack >= 142, "the root's children must be safe");
+
+// group entry: first node, mask (bits 0-15) | child count (16-19) | level of the nodes (20-24)
+__device__ inline uint32_t pack_group(uint32_t mask, uint32_t nchild, uint32_t level)
+{
+    return mask | (nchild << 16) | (level << 20);
+}
+
+template <bool F64, int T, bool ADJ>
+__global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
+{
+    constexpr int S = 64 / T;
+    constexpr uint32_t kMaskT = (1u << T) - 1u;
+    using R = typename std::conditional<F64, double, float>::type;
+    struct __align__(16) Rec { R x, y, z, m; };
+    constexpr int kRec = 64 + 2 * S;  // lists A and M, each padded to whole runs of S
+    __shared__ uint2 stk[kSplitWaves][kSplitStack];
+    __shared__ Rec rec[kSplitWaves][kRec];
+    __shared__ uint32_t rmask[kSplitWaves][kRec];  // targets (bits 0-15) | staging lane << 16
+    __shared__ R stau[kSplitWaves][64];            // by staging lane: opening threshold,
+    __shared__ uint2 srange[kSplitWaves][64];      // first particle and count,
+    __shared__ uint32_t somask[kSplitWaves][64];   // targets that open the child
+    __shared__ uint32_t rnode[ADJ ? kSplitWaves : 1][ADJ ? kRec : 1];
+
+    const int w = (int)(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t t = lane % T, s = lane / T;
+    const uint32_t tbit = 1u << t;
+    const int64_t wave_id = (int64_t)blockIdx.x * kSplitWaves + w;
+    const int64_t base = wave_id * T;
+    if (base >= a.n) return;  // whole wave; no block barrier follows
+    R tau0;
+    if constexpr (F64) tau0 = a.tau0_64;
+    else tau0 = a.tau0_32;
+
+    const bool valid = base + t < a.n;
+    const uint32_t first_t = uni(a.order[base]);
+    const uint32_t su = valid ? a.order[base + t] : first_t;
+    const Particle self = a.sp[su];
+    double Ax = 0.0, Ay = 0.0, Az = 0.0;
+    R px, py, pz;
+    if constexpr (F64) {
+        px = self.x; py = self.y; pz = self.z;
+    } else {
+        const Particle anchor = a.sp[uni(a.order[base & ~(int64_t)63])];
+        Ax = anchor.x; Ay = anchor.y; Az = anchor.z;
+        px = (float)(self.x - Ax); py = (float)(self.y - Ay); pz = (float)(self.z - Az);
+    }
+    const R eps2 = (R)a.eps2;
+    const R Gc = (R)a.G;
+    R gxl = 0, gyl = 0, gzl = 0, hl = 0;  // adjoint: G dL/da and G dL/dphi of this lane's target
+    if constexpr (ADJ) {
+        if (valid) {
+            const uint32_t i = a.perm[su];
+            const R* ga = (const R*)a.g_acc;
+            gxl = Gc * ga[3 * (int64_t)i + 0];
+            gyl = Gc * ga[3 * (int64_t)i + 1];
+            gzl = Gc * ga[3 * (int64_t)i + 2];
+            if (a.g_pot) hl = Gc * ((const R*)a.g_pot)[i];
+        }
+    }
+    // the sorted range the targets span and their bounding box (see walk.hip)
+    uint32_t smin = su, smax = su;
+    R bnx = px, bny = py, bnz = pz, bxx = px, bxy = py, bxz = pz;
+#pragma unroll
+    for (int o = T / 2; o > 0; o >>= 1) {
+        smin = min(smin, (uint32_t)__shfl_xor((int)smin, o, 64));
+        smax = max(smax, (uint32_t)__shfl_xor((int)smax, o, 64));
+        bnx = fmin(bnx, __shfl_xor(bnx, o, 64)); bny = fmin(bny, __shfl_xor(bny, o, 64));
+        bnz = fmin(bnz, __shfl_xor(bnz, o, 64)); bxx = fmax(bxx, __shfl_xor(bxx, o, 64));
+        bxy = fmax(bxy, __shfl_xor(bxy, o, 64)); bxz = fmax(bxz, __shfl_xor(bxz, o, 64));
+    }
+    const uint32_t wave_lo = smin, wave_end = smax + 1u;
+
+    R tx = 0, ty = 0, tz = 0, tp = 0;  // totals (F32C: with compensations), plain partial sums
+    float cx = 0.f, cy = 0.f, cz = 0.f, cp = 0.f;
+    R bx = 0, by = 0, bz = 0, bp = 0;
+    bool stack_over = false, corrupt = false;
+
+    // one accepted entry: the term (or its adjoint) of the active lanes
+    auto term = [&](const bool on, const Rec& e, const R dx, const R dy, const R dz, const R q, const uint32_t node) {
+        if constexpr (!ADJ) {
+            if (on) {
+                const R ri = rsqrt_any(q);
+                const R mr = e.m * ri;
+                const R mr3 = mr * (ri * ri);
+                bx = fma(mr3, dx, bx);
+                by = fma(mr3, dy, by);
+                bz = fma(mr3, dz, bz);
+                bp -= mr;
+            }
+        } else {
+            R sx = 0, sy = 0, sz = 0, sm = 0;
+            if (on) {
+                adj_term(dx, dy, dz, q, e.m, gxl, gyl, gzl, hl, sx, sy, sz, sm);
+                bx -= sx;
+                by -= sy;
+                bz -= sz;
+            }
+            // sums over the T targets of the slot; four of its lanes add one component each
+            const bool any = __ballot(on) >> (s * T) & kMaskT;
+            sx = slot_sum<T>(sx); sy = slot_sum<T>(sy); sz = slot_sum<T>(sz); sm = slot_sum<T>(sm);
+            const R v = t == 0 ? sx : t == 1 ? sy : t == 2 ? sz : sm;
+            if (any && t < 4) unsafeAtomicAdd(a.node_grad + 4 * (int64_t)node + t, (double)v);
+        }
+    };
+
+    int sp = 0;
+    const uint32_t rmeta = uni(a.nodes[0].meta);
+    if (!meta_leaf(rmeta)) {
+        const uint32_t live = (uint32_t)__ballot(valid) & kMaskT;
+        if (lane == 0) stk[w][0] = make_uint2(uni(a.nodes[0].child), pack_group(live, meta_nchild(rmeta), 1u));
+        sp = 1;
+    }
+    wave_sync();
+
+    const uint32_t gj = lane >> 3, gk = lane & 7;
+    int since_fold = 0;
+    while (sp > 0) {
+        // take the groups that the stack bound allows off the top; lanes 8 j .. 8 j + 7 stage group j
+        uint2 e = make_uint2(0u, 0u);
+        bool ok = false;
+        if ((int)gj < sp) {
+            e = stk[w][sp - 1 - (int)gj];
+            const int l = (int)((e.y >> 20) & 31u);
+            ok = gj == 0 || sp + 7 * ((int)gj + 1) + 7 * (20 - l) + 1 <= kSplitStack;
+        }
+        const uint64_t okm = __ballot(ok);
+        const int ng = ~okm ? (int)(__builtin_ctzll(~okm) >> 3) : 8;
+        sp = uni(sp - ng);
+        const uint32_t nc = (e.y >> 16) & 15u, pmask = e.y & 0xFFFFu;
+        const bool live = (int)gj < ng && gk < min(nc, 8u);
+        if (__ballot(live && nc > 8u)) corrupt = true;
+        bool far_all = false, near_all = false;
+        uint32_t child = 0, meta = 0, first = 0, count = 0;
+        Rec h;
+        const uint32_t node = e.x + gk;
+        if (live) {
+            const WalkNode nd = a.nodes[node];
+            if constexpr (F64) {
+                h.x = nd.x; h.y = nd.y; h.z = nd.z; h.m = nd.m;
+            } else {
+                h.x = (float)(nd.x - Ax); h.y = (float)(nd.y - Ay); h.z = (float)(nd.z - Az);
+                h.m = (float)nd.m;
+            }
+            first = nd.first;
+            count = nd.count;
+            child = nd.child;
+            meta = nd.meta;
+            const bool ovl = first < wave_end && first + count > wave_lo;
+            const R tau = meta_single(meta) ? (R)-1 : (R)ldexp(tau0, -2 * (int)meta_level(meta));
+            stau[w][lane] = tau;
+            srange[w][lane] = make_uint2(first, count);
+            // the box test of walk.hip: decided for every target of the wavefront
+            const R gx = fmax(fmax(bnx - h.x, h.x - bxx), (R)0), fx = fmax(fabs(h.x - bnx), fabs(h.x - bxx));
+            const R gy = fmax(fmax(bny - h.y, h.y - bxy), (R)0), fy = fmax(fabs(h.y - bny), fabs(h.y - bxy));
+            const R gz = fmax(fmax(bnz - h.z, h.z - bxz), (R)0), fz = fmax(fabs(h.z - bnz), fabs(h.z - bxz));
+            far_all = !ovl && fma(gx, gx, fma(gy, gy, gz * gz)) > tau;
+            near_all = !far_all && !(fma(fx, fx, fma(fy, fy, fz * fz)) > tau);
+        }
+        const bool mixed = live && !far_all && !near_all;
+        const uint64_t fm = __ballot(far_all), mm = __ballot(mixed);
+        const int na = (int)__popcll(fm), nm = (int)__popcll(mm);
+        const int na_pad = (na + S - 1) & ~(S - 1), end = na_pad + ((nm + S - 1) & ~(S - 1));
+        if (far_all || mixed) {
+            const uint32_t at = far_all ? popc_below(fm) : (uint32_t)na_pad + popc_below(mm);
+            rec[w][at] = h;
+            rmask[w][at] = pmask | (lane << 16);
+            if constexpr (ADJ) rnode[w][at] = node;
+        }
+        if ((int)lane < na_pad - na) rmask[w][na + (int)lane] = 0u;
+        if ((int)lane < end - na_pad - nm) rmask[w][na_pad + nm + (int)lane] = 0u;
+        wave_sync();
+
+        // list A: accepted by every target of the entry's mask
+        {
+            Rec hc = rec[w][s];
+            uint32_t mc = rmask[w][s];
+            for (int e0 = 0; e0 < na_pad; e0 += S) {
+                // the next run's entry is read while this one is evaluated (the last read may fall
+                // into list M or past it, within the array, and is not used)
+                const Rec hn = rec[w][e0 + S + (int)s < kRec ? e0 + S + (int)s : 0];
+                const uint32_t mn = rmask[w][e0 + S + (int)s < kRec ? e0 + S + (int)s : 0];
+                const R dx = hc.x - px, dy = hc.y - py, dz = hc.z - pz;
+                term((mc & tbit) != 0u, hc, dx, dy, dz, fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2))),
+                     ADJ ? rnode[ADJ ? w : 0][ADJ ? e0 + (int)s : 0] : 0u);
+                hc = hn;
+                mc = mn;
+            }
+        }
+        // list M: the per-target rule (walk.hip: accepted = active, not containing, far enough)
+        for (int e0 = na_pad; e0 < end; e0 += S) {
+            const Rec hc = rec[w][e0 + (int)s];
+            const uint32_t mc = rmask[w][e0 + (int)s];
+            const uint32_t src = mc >> 16;
+            const uint2 fr = srange[w][src];
+            const R tau = stau[w][src];
+            const R dx = hc.x - px, dy = hc.y - py, dz = hc.z - pz;
+            const R d2 = fma(dx, dx, fma(dy, dy, dz * dz));
+            const bool active = (mc & tbit) != 0u;
+            const bool take = active && d2 > tau && !((su - fr.x) < fr.y);
+            term(take, hc, dx, dy, dz, d2 + eps2, ADJ ? rnode[ADJ ? w : 0][ADJ ? e0 + (int)s : 0] : 0u);
+            const uint64_t om = __ballot(active && !take);
+            if (t == 0 && (mc & kMaskT)) somask[w][src] = (uint32_t)(om >> (s * T)) & kMaskT;
+        }
+        wave_sync();
+
+        // opened children push their groups; an opened multi-particle leaf's particles are taken one by one
+        uint32_t open = 0u;
+        if (near_all) open = pmask;
+        else if (mixed) open = somask[w][lane];
+        const bool leaf = meta_leaf(meta);
+        const uint64_t pm = __ballot(open != 0u && !leaf);
+        const int np = (int)__popcll(pm);
+        if (sp + np > kSplitStack) {
+            stack_over = true;  // cannot happen (see the bound); refused and flagged
+        } else {
+            if (open != 0u && !leaf)
+                stk[w][sp + (int)popc_below(pm)] =
+                    make_uint2(child, pack_group(open, meta_nchild(meta), meta_level(meta) + 1u));
+            sp = uni(sp + np);
+        }
+        for (uint64_t lm = __ballot(open != 0u && leaf && count > 1u); lm; lm &= lm - 1ull) {
+            const int src = (int)__builtin_ctzll(lm);
+            const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)first, src);
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)count, src);
+            const uint32_t om = (uint32_t)__builtin_amdgcn_readlane((int)open, src);
+            const bool lane_open = (om & tbit) != 0u;
+            for (uint32_t j0 = 0; j0 < cnt; j0 += S) {
+                // separations in FP64: the particles share a level-21 cell (see walk.hip)
+                const uint32_t j = f + j0 + s;
+                const bool in = j0 + s < cnt;
+                const Particle pj = a.sp[in ? j : f];
+                const bool on = in && lane_open && j != su;
+                R sx = 0, sy = 0, sz = 0, sm = 0;
+                if (on) {
+                    const Particle me = a.sp[su];
+                    const R mj = (R)pj.m;
+                    const R ex = (R)(pj.x - me.x), ey = (R)(pj.y - me.y), ez = (R)(pj.z - me.z);
+                    const R q = fma(ex, ex, fma(ey, ey, ez * ez)) + eps2;
+                    if constexpr (!ADJ) {
+                        const R ri = rsqrt_any(q);
+                        const R mr = mj * ri;
+                        const R mr3 = mr * (ri * ri);
+                        bx = fma(mr3, ex, bx);
+                        by = fma(mr3, ey, by);
+                        bz = fma(mr3, ez, bz);
+                        bp -= mr;
+                    } else {
+                        adj_term(ex, ey, ez, q, mj, gxl, gyl, gzl, hl, sx, sy, sz, sm);
+                        bx -= sx;
+                        by -= sy;
+                        bz -= sz;
+                    }
+                }
+                if constexpr (ADJ) {
+                    sx = slot_sum<T>(sx); sy = slot_sum<T>(sy); sz = slot_sum<T>(sz); sm = slot_sum<T>(sm);
+                    const R v = t == 0 ? sx : t == 1 ? sy : t == 2 ? sz : sm;
+                    if (in && t < 4) unsafeAtomicAdd(a.part_grad + 4 * (int64_t)j + t, (double)v);
+                }
+            }
+        }
+        wave_sync();
+        // at most 64 / S terms a lane and step go into the plain sums
+        if (++since_fold == 2 || sp == 0) {
+            since_fold = 0;
+            if constexpr (F64) {
+                tx += bx; ty += by; tz += bz; tp += bp;
+            } else {
+                kahan_add(tx, cx, bx);
+                kahan_add(ty, cy, by);
+                kahan_add(tz, cz, bz);
+                kahan_add(tp, cp, bp);
+            }
+            bx = 0; by = 0; bz = 0; bp = 0;
+        }
+    }
+    if (lane == 0 && (stack_over || corrupt)) atomicOr(a.status, (stack_over ? 1u : 0u) | (corrupt ? 2u : 0u));
+
+    // the slots' totals, added in FP64
+    double v[4];
+    if constexpr (F64) {
+        v[0] = tx; v[1] = ty; v[2] = tz; v[3] = tp;
+    } else {
+        v[0] = (double)tx - (double)cx; v[1] = (double)ty - (double)cy;
+        v[2] = (double)tz - (double)cz; v[3] = (double)tp - (double)cp;
+    }
+#pragma unroll
+    for (int o = T; o < 64; o <<= 1)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += __shfl_xor(v[k], o, 64);
+
+    if constexpr (ADJ) {
+        if (valid && s == 0) {
+            double* tg = a.target_grad + 3 * (int64_t)su;
+            tg[0] = v[0]; tg[1] = v[1]; tg[2] = v[2];
+        }
+    } else {
+        double dm[4] = {0.0, 0.0, 0.0, 0.0};
+        if (valid && s == 0) {
+            const R ox = (R)v[0] * Gc, oy = (R)v[1] * Gc, oz = (R)v[2] * Gc, op = (R)v[3] * Gc;
+            const uint32_t i = a.perm[su];
+            R* acc = (R*)a.acc;
+            acc[3 * (int64_t)i + 0] = ox;
+            acc[3 * (int64_t)i + 1] = oy;
+            acc[3 * (int64_t)i + 2] = oz;
+            if (a.pot) ((R*)a.pot)[i] = op;
+            const double m = self.m;
+            const double ex = (double)ox, ey = (double)oy, ez = (double)oz;
+            dm[0] = m * ex;
+            dm[1] = m * ey;
+            dm[2] = m * ez;
+            dm[3] = m * sqrt(ex * ex + ey * ey + ez * ez);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) dm[k] = wave_sum(dm[k]);
+        if (lane == 0) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) a.diag[4 * wave_id + k] = dm[k];
+        }
+    }
+}
+
+template <int T, bool ADJ>
+void launch_split(const WalkArgs& a, tc_walk mode, hipStream_t s)
+{
+    const int64_t waves = (a.n + T - 1) / T;
+    const unsigned blocks = (unsigned)((waves + kSplitWaves - 1) / kSplitWaves);
+    if (mode == TC_WALK_F64) k_walk_split<true, T, ADJ><<<blocks, kSplitThreads, 0, s>>>(a);
+    else k_walk_split<false, T, ADJ><<<blocks, kSplitThreads, 0, s>>>(a);
+}
+
+}  // namespace
+
+// Where the lines lie (walk times in us on one MI355X, theta = 0.6 up to 2^18 and
+// 0.5 above, T = 8 / 16 / 64):
+//   F32C  16384: 54 / 78 / 328    65536: 118 / 108 / 365    262144: 408 / 324 / 449
+//         524288: 1247 / 933 / 989    1000000: 2334 / 1717 / 1663
+//   FP64  16384: 62 / 83 / 404    65536: 162 / 153 / 459    262144: 581 / 485 / 705
+//         1000000: 3360 / 2764 / 2953    4000000: 13900 / 11281 / 10704
+// The FP64 term costs about twice the FP32 one and the staging the same, so the
+// better-filled lanes of 16 targets pay for longer there.
+int walk_targets(int64_t n, tc_walk mode)
+{
+    if (n <= 49152) return 8;
+    return n <= (mode == TC_WALK_F64 ? 1 << 21 : 1 << 19) ? 16 : 64;
+}
+
+// The adjoint adds to a node's gradient with four atomics per wavefront and node,
+// so fewer targets a wavefront mean more atomics (us, T = 8 / 16 / 64):
+//   F32C  1000: 62 / 85 / 361    16384: 242 / 177 / 727    65536: 804 / 576 / 868
+//         131072: 1396 / 1037 / 1004
+//   FP64  16384: 225 / 205 / 885    131072: 1501 / 1136 / 1317    262144: 2912 / 1846 / 2030
+int adjoint_targets(int64_t n, tc_walk mode)
+{
+    if (n <= 4096) return 8;
+    return n <= (mode == TC_WALK_F64 ? 1 << 18 : 3 << 15) ? 16 : 64;
+}
+
+void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s)
+{
+    if (a.n == 0) return;
+    if (targets == 8) launch_split<8, false>(a, mode, s);
+    else launch_split<16, false>(a, mode, s);
+}
+
+void launch_walk_split_adjoint(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s)
+{
+    if (a.n == 0) return;
+    if (targets == 8) launch_split<8, true>(a, mode, s);
+    else launch_split<16, true>(a, mode, s);
+}
+
+}  // namespace tc

@@ -1,0 +1,78 @@
+"""The walks with 8 or 16 targets a wavefront (small inputs, no counting, no
+stored lists) against the FP64 oracle, at sizes around one wavefront's targets,
+with multi-particle leaves, the direct sum, and on both sides of the sizes at
+which the library changes the number of targets (there against the 64-target
+walk, which the counting walk always uses: the decisions are the same, so the
+outputs may differ by rounding only).  Bars: tests/bars.py."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from bars import check_errors, rel_err
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+def _dups(n, seed):
+    g = np.random.default_rng(seed)
+    pos = g.random((n, 3))
+    pos[n // 3:n // 3 + 21] = pos[0]  # a leaf of 22 particles
+    pos[n // 2:n // 2 + 3] = pos[5] + 1e-9
+    return pos, np.full(n, 1.0 / n)
+
+
+CASES = [("n%d" % n, lambda n=n: workloads.plummer(n, 500 + n), 0.6, 0.05) for n in (2, 7, 8, 9, 17, 63, 65, 1001)]
+CASES += [
+    ("dups4097", lambda: _dups(4097, 4), 0.6, 0.001),
+    ("direct3001", lambda: workloads.plummer(3001, 77), 0.0, 0.01),
+    ("disc", lambda: workloads.disc_galaxy(5000, 1003, 5, dtype=np.float32)[0::2], 1.2, 0.02),
+]
+
+
+def _gpu(pos, m):
+    d = torch.device("cuda:0")
+    return torch.from_numpy(np.ascontiguousarray(pos)).to(d), torch.from_numpy(np.ascontiguousarray(m)).to(d)
+
+
+@pytest.mark.parametrize("walk", ["f32c", "f64"])
+@pytest.mark.parametrize("name,make,theta,eps", CASES, ids=[c[0] for c in CASES])
+def test_split_walks_match_oracle(name, make, theta, eps, walk):
+    import paper_2412_01733_amd as tc
+    print("case", name, walk, flush=True)
+    pos, m = make()
+    p, mm = _gpu(pos, m)
+    _, _, tree = tc.forces(p, mm, theta, eps, walk=walk, count=True)
+    counts = tree.interaction_counts().cpu().numpy().astype(np.int64)
+    acc, pot = tree.forces(theta, eps, walk=walk)
+    T = oracle.Tree(pos, m)
+    ra, rp, nint = T.forces(theta, eps)
+    same = counts == nint
+    check_errors(rel_err(acc.cpu().numpy(), ra), walk, same, "acc")
+    check_errors(rel_err(pot.cpu().numpy(), rp), walk, same, "pot")
+    again, _ = tree.forces(theta, eps, walk=walk)
+    assert torch.equal(acc, again)
+    g = np.random.default_rng(11)
+    ga, gp = g.standard_normal(pos.shape), g.standard_normal(len(pos))
+    gx, gm = tree.backward(torch.from_numpy(ga).to(p.device), torch.from_numpy(gp).to(p.device))
+    ox, om = T.frozen_adjoint(T.lists(theta), eps, ga, gp)
+    check_errors(rel_err(gx.cpu().numpy(), ox), walk, what="dL/dx", per_target=False)
+    check_errors(rel_err(gm.cpu().numpy(), om), walk, what="dL/dm", per_target=False)
+    st = tree.stats()
+    md = np.asarray(m, np.float64)
+    assert abs(st["sum_m_abs_a"] / (md * np.linalg.norm(ra, axis=1)).sum() - 1) < 1e-6
+
+
+@pytest.mark.parametrize("walk,n", [("f32c", 49152), ("f32c", 49153), ("f32c", 524288), ("f32c", 524289),
+                                    ("f64", 49153), ("f64", 2097152), ("f64", 2097153)])
+def test_both_sides_of_the_lines(walk, n):
+    import paper_2412_01733_amd as tc
+    print("case", walk, n, flush=True)
+    p, mm = _gpu(*workloads.plummer(n, 9, dtype=np.float32))
+    tree = tc.Tree()
+    tree.build(p, mm).moments()
+    a64, p64 = tree.forces(0.7, 0.01, walk=walk, count=True)
+    acc, pot = tree.forces(0.7, 0.01, walk=walk)
+    check_errors(rel_err(acc.cpu().numpy(), a64.cpu().numpy()), walk, what="acc")
+    check_errors(rel_err(pot.cpu().numpy(), p64.cpu().numpy()), walk, what="pot")
