@@ -18,11 +18,11 @@ namespace tc {
 namespace {
 
 #define ADJ_ARGS                                                                                            \
-    const WalkNode *__restrict__ wn, const uint32_t *__restrict__ parent, const double *__restrict__ node_grad, \
+    const WalkNode *__restrict__ wn, const uint2 *__restrict__ up, const double *__restrict__ node_grad, \
         double *__restrict__ uc, const Particle *__restrict__ sp, const uint32_t *__restrict__ perm,          \
         const double *__restrict__ target_grad, const double *__restrict__ part_grad, void *__restrict__ g_pos, \
         void *__restrict__ g_mass
-#define ADJ_PASS wn, parent, node_grad, uc, sp, perm, target_grad, part_grad, g_pos, g_mass
+#define ADJ_PASS wn, up, node_grad, uc, sp, perm, target_grad, part_grad, g_pos, g_mass
 
 template <bool OUT64>
 __device__ inline void adjoint_node(int64_t b, bool root, ADJ_ARGS)
@@ -37,11 +37,11 @@ __device__ inline void adjoint_node(int64_t b, bool root, ADJ_ARGS)
     }
     double c = gn[3] - (u0 * nd.x + u1 * nd.y + u2 * nd.z);
     if (!root) {
-        const double* up = uc + 4 * (int64_t)parent[b];
-        u0 += up[0];
-        u1 += up[1];
-        u2 += up[2];
-        c += up[3];
+        const double* above = uc + 4 * (int64_t)up[b].y;
+        u0 += above[0];
+        u1 += above[1];
+        u2 += above[2];
+        c += above[3];
     }
     double* mine = uc + 4 * b;
     mine[0] = u0;
@@ -113,7 +113,7 @@ void launch_fill_f64_zero(double* p, int64_t n, hipStream_t s)
     k_zero_f64<<<(unsigned)b, 256, 0, s>>>(p, n);
 }
 
-void launch_adjoint_down(const uint32_t* level_off_host, const WalkNode* wn, const uint32_t* parent,
+void launch_adjoint_down(const uint32_t* level_off_host, const WalkNode* wn, const uint2* up,
                          const double* node_grad, double* uc, const Particle* sp, const uint32_t* perm,
                          const double* target_grad, const double* part_grad,
                          void* g_pos, void* g_mass, bool out_f64, hipStream_t s)

@@ -1,4 +1,4 @@
-// Bottom-up octree construction from sorted Morton keys.
+// Octree construction from sorted Morton keys.
 //
 // The tree is the canonical octree of the TreeCode description (section 2):
 // a level-l cell (particles sharing the top 3l key bits) is a node iff it is
@@ -8,220 +8,230 @@
 //
 // With c_s = the deepest level at which keys s and s+1 share a cell
 // (c_s = min(21, floor((clz64(k_s ^ k_{s+1}) - 1) / 3)), c_{-1} = c_{n-1} = -1),
-// the nodes whose first particle is s are exactly the levels
-//   c_{s-1} + 1 ... min(21, max(c_{s-1}, c_s) + 1),
-// so the node count per particle is local and the pre-order index of every
-// node is an exclusive scan over s (pre-order = order by (first, level)).
-// A node's end is found by galloping search on the keys, and its skip link
-// ("next") is the pre-order index of the first node starting at its end.
+// particle s lies in nodes of the levels 0 ... m_s = min(21, max(c_{s-1}, c_s) + 1),
+// is the first particle of those of levels c_{s-1} + 1 ... m_s and the last of
+// those of levels c_s + 1 ... m_s.
 //
 // The walk wants siblings contiguous and the upward pass wants each level
-// contiguous, so the walk's node array is in breadth-first order: sorted by
-// (level, first), obtained by one stable 8-bit radix pass on the level of
-// the pre-order nodes.  The children of pre-order node p then start at the
-// breadth-first index of p + 1 and are consecutive.
+// contiguous, so nodes are numbered breadth first: by (level, first).  The
+// level-l node that holds s is then number
+//   off_l + (level-l nodes whose first particle is <= s) - 1,
+// a count that a block gets from ballots, one per level, on top of the counts
+// of the blocks before it.  So every particle knows the number of each node that
+// begins or ends with it, of its parent and of its child there, and writes
+// them down: no sort by level, no search for a node's end, no links to follow.
+// (At 1e7 particles the tree and the upward pass took 1.92 ms with a radix pass
+// over the levels, a galloping search per node and gathers through the pre-order
+// numbers; see moments.hip for the present figures.)
 #include "tc_internal.h"
+#include "walk_common.h"
 
 namespace tc {
 namespace {
 
+constexpr int kTreeThreads = 1024;  // a particle each
+constexpr int kTreeWaves = kTreeThreads / 64;
+
 inline unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
-__global__ __launch_bounds__(256) void k_adjacent(const uint64_t* __restrict__ k, int64_t n,
-                                                  int8_t* __restrict__ c)
+__device__ inline int shared_level(uint64_t a, uint64_t b)
 {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    if (s == n - 1) {
-        c[s] = -1;
-        return;
-    }
-    uint64_t x = k[s] ^ k[s + 1];
-    int lv = 21;
-    if (x != 0) {
-        int z = __clzll((long long)x);
-        lv = (z - 1) / 3;
-        if (lv > 21) lv = 21;
-    }
-    c[s] = (int8_t)lv;
+    const uint64_t x = a ^ b;
+    return x ? (__clzll((long long)x) - 1) / 3 : kMaxLevel;
 }
 
-__device__ inline void node_range(const int8_t* c, int64_t s, int& lo, int& hi)
-{
-    int cp = s > 0 ? (int)c[s - 1] : -1;
-    int cs = (int)c[s];
-    lo = cp + 1;
-    int m = cp > cs ? cp : cs;
-    hi = m + 1 < kMaxLevel ? m + 1 : kMaxLevel;
-}
+// c_{s-1}, c_s and m_s of particle s.
+struct Span {
+    int before, after, deepest;
+};
 
-// Node count per first particle, plus a histogram of node levels and the
-// leaf counts (counted per wave with ballots, then one atomic per entry and
-// block).  hist[0..21]: nodes per level; hist[22]: leaves; hist[23]:
-// multi-particle leaves.  The deepest node starting at s is always a leaf,
-// and it holds several particles iff it sits at level 21 and s + 1 shares it.
-__global__ __launch_bounds__(256) void k_node_counts(const int8_t* __restrict__ c, int64_t n,
-                                                     uint32_t* __restrict__ cnt,
-                                                     uint32_t* __restrict__ level_hist)
+__device__ inline Span particle_span(const uint64_t* __restrict__ k, int64_t n, int64_t s)
 {
-    constexpr int kH = kLevels + 2;
-    __shared__ uint32_t h[256 / 64][kH];
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint32_t acc = 0;  // lane l < kH of each wave accumulates entry l
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t start = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int64_t s0 = start - threadIdx.x; s0 < n; s0 += stride) {
-        const int64_t s = s0 + threadIdx.x;
-        int lo = 1, hi = 0, cs = -1;
-        if (s < n) {
-            node_range(c, s, lo, hi);
-            cs = (int)c[s];
-            int k = hi - lo + 1;
-            cnt[s] = (uint32_t)(k > 0 ? k : 0);
-        }
-        for (int l = 0; l < kLevels; ++l) {
-            const uint32_t b = (uint32_t)__popcll(__ballot(lo <= l && l <= hi));
-            if (lane == l) acc += b;
-        }
-        const uint32_t bl = (uint32_t)__popcll(__ballot(lo <= hi));
-        const uint32_t bm = (uint32_t)__popcll(__ballot(lo <= hi && hi == kMaxLevel && cs == kMaxLevel));
-        if (lane == kLevels) acc += bl;
-        if (lane == kLevels + 1) acc += bm;
-    }
-    if (lane < kH) h[w][lane] = acc;
-    __syncthreads();
-    if (threadIdx.x < kH) {
-        uint32_t t = 0;
-        for (int ww = 0; ww < 256 / 64; ++ww) t += h[ww][threadIdx.x];
-        if (t) atomicAdd(&level_hist[threadIdx.x], t);
-    }
-}
-
-// First index j > s whose level-l prefix differs from that of key (or n).
-// The caller guarantees that s + 1 < n shares the prefix.
-__device__ inline int64_t cell_end(const uint64_t* __restrict__ k, int64_t n, int64_t s, uint64_t key, int l)
-{
-    const int sh = 3 * (kMaxLevel - l);
-    const uint64_t P = key >> sh;
-    int64_t in = s + 1;  // known inside
-    int64_t step = 1;
-    int64_t probe = in + step;
-    while (probe < n && (k[probe] >> sh) == P) {
-        in = probe;
-        step <<= 1;
-        probe = in + step;
-    }
-    int64_t lo = in + 1, hi = probe < n ? probe : n;
-    while (lo < hi) {
-        int64_t mid = lo + ((hi - lo) >> 1);
-        if ((k[mid] >> sh) == P) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
-__global__ __launch_bounds__(256) void k_emit(const uint64_t* __restrict__ k, const int8_t* __restrict__ c,
-                                              const uint32_t* __restrict__ pre, int64_t n,
-                                              uint8_t* __restrict__ level, uint32_t* __restrict__ first,
-                                              uint32_t* __restrict__ count, uint32_t* __restrict__ next,
-                                              uint8_t* __restrict__ octant)
-{
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    int lo, hi;
-    node_range(c, s, lo, hi);
-    const int cs = (int)c[s];
+    Span r;
     const uint64_t key = k[s];
-    uint32_t p = pre[s];
-    for (int l = lo; l <= hi; ++l, ++p) {
-        int64_t end = (l > cs) ? s + 1 : cell_end(k, n, s, key, l);
-        level[p] = (uint8_t)l;
-        octant[p] = l > 0 ? (uint8_t)((key >> (3 * (kMaxLevel - l))) & 7u) : (uint8_t)0;  // key digit at level l
-        first[p] = (uint32_t)s;
-        count[p] = (uint32_t)(end - s);
-        next[p] = pre[end];
-    }
+    r.before = s > 0 ? shared_level(k[s - 1], key) : -1;
+    r.after = s + 1 < n ? shared_level(key, k[s + 1]) : -1;
+    const int m = (r.before > r.after ? r.before : r.after) + 1;
+    r.deepest = m < kMaxLevel ? m : kMaxLevel;
+    return r;
 }
 
-__device__ inline bool is_internal(uint8_t level, uint32_t count) { return count >= 2 && level < kMaxLevel; }
-
-// Children per node, walked through the skip links.
-__global__ __launch_bounds__(256) void k_count_children(const uint8_t* __restrict__ level,
-                                                        const uint32_t* __restrict__ count,
-                                                        const uint32_t* __restrict__ next, int64_t nn,
-                                                        uint32_t* __restrict__ nchild)
+// Per block: nodes that begin in it, by level (rows 0..21 of the table), leaves
+// (22) and multi-particle leaves (23; the leaf that begins at s holds several
+// particles iff it sits at level 21 and s + 1 shares it).  A lone block's counts
+// are the totals.
+__global__ __launch_bounds__(kTreeThreads) void k_tree_counts(const uint64_t* __restrict__ k, int64_t n,
+                                                              uint32_t* __restrict__ table, uint32_t* __restrict__ totals)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nn) return;
-    if (!is_internal(level[p], count[p])) {
-        nchild[p] = 0;
-        return;
+    __shared__ uint32_t h[kTreeWaves][kTreeRows];
+    const int64_t s = (int64_t)blockIdx.x * kTreeThreads + threadIdx.x;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    Span sp = {kMaxLevel, -1, 0};  // begins nothing
+    if (s < n) sp = particle_span(k, n, s);
+    uint32_t acc = 0;  // lane l keeps row l
+    for (int l = 0; l < kLevels; ++l) {
+        const uint32_t b = (uint32_t)__popcll(__ballot(sp.before < l && l <= sp.deepest));
+        if (lane == l) acc = b;
     }
-    uint32_t e = next[p], ch = (uint32_t)p + 1, k = 0;
-    while (ch < e) {
-        ++k;
-        ch = next[ch];
+    const bool leaf = sp.before < sp.deepest;
+    const uint32_t bl = (uint32_t)__popcll(__ballot(leaf));
+    const uint32_t bm = (uint32_t)__popcll(__ballot(leaf && sp.after == kMaxLevel));
+    if (lane == kLevels) acc = bl;
+    if (lane == kLevels + 1) acc = bm;
+    if (lane < kTreeRows) h[w][lane] = acc;
+    __syncthreads();
+    if (threadIdx.x < kTreeRows) {
+        uint32_t t = 0;
+        for (int u = 0; u < kTreeWaves; ++u) t += h[u][threadIdx.x];
+        if (gridDim.x == 1) {
+            totals[threadIdx.x] = t;
+            t = 0;
+        }
+        table[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = t;
     }
-    nchild[p] = k;
 }
 
-// Sort input for the breadth-first permutation: key = level, value = p.
-__global__ __launch_bounds__(256) void k_level_keys(const uint8_t* __restrict__ level, int64_t nn,
-                                                    uint64_t* __restrict__ keys, uint32_t* __restrict__ vals)
+// Writes down the nodes (see above).  topo[b] = {first particle, first child,
+// meta, 0} comes from the node's first particle, ends[b] = {end, last child} from
+// its last one (not for one-particle leaves, whose walk record is complete here);
+// leaf_of[s] is the leaf that holds s.
+// Bound by HBM: 8 + 32 bytes read, 4 + 48 written a particle, 24 a node.
+__global__ __launch_bounds__(kTreeThreads) void k_emit(const uint64_t* __restrict__ k, int64_t n,
+                                                       const uint32_t* __restrict__ table, LevelOffsets off,
+                                                       const Particle* __restrict__ sp, uint4* __restrict__ topo,
+                                                       uint2* __restrict__ ends, WalkNode* __restrict__ wn,
+                                                       uint32_t* __restrict__ leaf_of, uint32_t* __restrict__ status)
 {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nn) return;
-    keys[p] = level[p];
-    vals[p] = (uint32_t)p;
+    __shared__ uint64_t begins[kTreeWaves][kLevels];  // lanes whose particle begins a level-l node
+    __shared__ uint32_t before[kTreeWaves][kLevels];  // number of the next level-l node at the wave's start
+    const int64_t s = (int64_t)blockIdx.x * kTreeThreads + threadIdx.x;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (s == 0) *status = 0u;  // a build clears the walks' status word
+    Span span = {kMaxLevel, -1, 0};
+    uint64_t key = 0;
+    if (s < n) {
+        span = particle_span(k, n, s);
+        key = k[s];
+    }
+    uint64_t mine = 0;
+    for (int l = 0; l < kLevels; ++l) {
+        const uint64_t b = __ballot(span.before < l && l <= span.deepest);
+        if (lane == l) mine = b;
+    }
+    if (lane < kLevels) begins[w][lane] = mine;
+    __syncthreads();
+    if (threadIdx.x < kLevels) {
+        const int l = threadIdx.x;
+        uint32_t t = off.off[l] + table[(int64_t)l * gridDim.x + blockIdx.x];
+        for (int u = 0; u < kTreeWaves; ++u) {
+            before[u][l] = t;
+            t += (uint32_t)__popcll(begins[u][l]);
+        }
+    }
+    __syncthreads();
+    if (s >= n) return;
+    // number of the level-l node that holds s
+    const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;
+    auto number = [&](int l) { return before[w][l] + (uint32_t)__popcll(begins[w][l] & upto) - 1u; };
+    const int lowest = (span.before < span.after ? span.before : span.after) + 1;
+    uint32_t below = 0;  // number of the node one level down
+    for (int l = span.deepest; l >= lowest; --l) {
+        const uint32_t b = number(l);
+        const bool leaf = l == span.deepest;
+        if (leaf) leaf_of[s] = b;
+        const bool single = leaf && span.before < l && span.after < l;
+        if (span.before < l) {
+            const uint32_t oct = l > 0 ? (uint32_t)((key >> (3 * (kMaxLevel - l))) & 7u) : 0u;
+            const uint32_t meta = ((uint32_t)l << 8) | (single ? (1u << 13) | (1u << 17) : 0u) | (leaf ? 1u << 16 : 0u) | (oct << 18);
+            topo[b] = make_uint4((uint32_t)s, leaf ? 0u : below, meta, 0u);
+            if (single) {
+                const double2* p = reinterpret_cast<const double2*>(sp + s);
+                double2* o = reinterpret_cast<double2*>(wn + b);
+                o[0] = p[0];
+                o[1] = p[1];
+                reinterpret_cast<uint4*>(wn + b)[2] = make_uint4((uint32_t)s, 1u, 0u, meta);
+            }
+        }
+        if (span.after < l && !single) ends[b] = make_uint2((uint32_t)s + 1u, leaf ? 0u : below);
+        below = b;
+    }
+    if (lowest > span.deepest) leaf_of[s] = number(span.deepest);  // inside a leaf of coincident keys
 }
 
-__global__ __launch_bounds__(256) void k_bfs_scatter(const uint32_t* __restrict__ bfs_to_pre, int64_t nn,
-                                                     uint32_t* __restrict__ bfs)
+// Pre-order number of the first node that begins at particle s (pre-order = by
+// (first, level), the order of the canonical export).
+__global__ __launch_bounds__(kTreeThreads) void k_preorder(const uint64_t* __restrict__ k, int64_t n,
+                                                           const uint32_t* __restrict__ table, uint32_t* __restrict__ pre)
+{
+    __shared__ uint32_t wsum[kTreeWaves];
+    const int64_t s = (int64_t)blockIdx.x * kTreeThreads + threadIdx.x;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    uint32_t c = 0;
+    if (s < n) {
+        const Span sp = particle_span(k, n, s);
+        c = sp.deepest > sp.before ? (uint32_t)(sp.deepest - sp.before) : 0u;
+    }
+    uint32_t inc = c;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t u = __shfl_up(inc, o, 64);
+        if (lane >= o) inc += u;
+    }
+    if (lane == 63) wsum[w] = inc;
+    __syncthreads();
+    uint32_t base = 0;
+    for (int l = 0; l < kLevels; ++l) base += table[(int64_t)l * gridDim.x + blockIdx.x];
+    for (int u = 0; u < w; ++u) base += wsum[u];
+    if (s < n) pre[s] = base + inc - c;
+}
+
+__global__ __launch_bounds__(256) void k_export_nodes(const uint64_t* __restrict__ k, int64_t n,
+                                                      const uint32_t* __restrict__ pre, const uint4* __restrict__ topo,
+                                                      const uint2* __restrict__ ends, const WalkNode* __restrict__ wn,
+                                                      int64_t nn, uint8_t* __restrict__ level, uint32_t* __restrict__ first,
+                                                      uint32_t* __restrict__ count, double* __restrict__ com,
+                                                      double* __restrict__ mass)
 {
     const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (b >= nn) return;
-    bfs[bfs_to_pre[b]] = (uint32_t)b;
+    const uint4 t = topo[b];
+    const int l = (int)meta_level(t.z);
+    const int64_t p = (int64_t)pre[t.x] + (l - 1 - (t.x > 0 ? shared_level(k[t.x - 1], k[t.x]) : -1));
+    if (level) level[p] = (uint8_t)l;
+    if (first) first[p] = t.x;
+    if (count) count[p] = meta_single(t.z) ? 1u : ends[b].x - t.x;
+    if (com) {
+        com[3 * p + 0] = wn[b].x;
+        com[3 * p + 1] = wn[b].y;
+        com[3 * p + 2] = wn[b].z;
+    }
+    if (mass) mass[p] = wn[b].m;
 }
 
 }  // namespace
 
-void launch_adjacent_levels(const uint64_t* skeys, int64_t n, int8_t* c, hipStream_t s)
+size_t tree_table_bytes(int64_t n) { return (size_t)grid_for(n, kTreeThreads) * kTreeRows * sizeof(uint32_t); }
+
+void launch_tree_counts(const uint64_t* skeys, int64_t n, uint32_t* table, uint32_t* totals, hipStream_t s)
 {
-    if (n == 0) return;
-    k_adjacent<<<grid_for(n, 256), 256, 0, s>>>(skeys, n, c);
+    const unsigned nb = grid_for(n, kTreeThreads);
+    k_tree_counts<<<nb, kTreeThreads, 0, s>>>(skeys, n, table, totals);
+    if (nb > 1) launch_scan_rows(table, kTreeRows, nb, totals, s);
 }
 
-void launch_node_counts(const int8_t* c, int64_t n, uint32_t* cnt, uint32_t* level_hist, hipStream_t s)
+void launch_emit(const uint64_t* skeys, int64_t n, const uint32_t* table, const uint32_t* level_off_host, const Particle* sp,
+                 uint4* topo, uint2* ends, WalkNode* wn, uint32_t* leaf_of, uint32_t* status, hipStream_t s)
 {
-    if (n == 0) return;
-    unsigned b = grid_for(n, 256);
-    if (b > 1024) b = 1024;
-    k_node_counts<<<b, 256, 0, s>>>(c, n, cnt, level_hist);
+    LevelOffsets off;
+    for (int l = 0; l <= kLevels; ++l) off.off[l] = level_off_host[l];
+    k_emit<<<grid_for(n, kTreeThreads), kTreeThreads, 0, s>>>(skeys, n, table, off, sp, topo, ends, wn, leaf_of, status);
 }
 
-void launch_emit_nodes(const uint64_t* skeys, const int8_t* c, const uint32_t* pre, int64_t n,
-                       uint8_t* level, uint32_t* first, uint32_t* count, uint32_t* next, uint8_t* octant,
-                       hipStream_t s)
+void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table, uint32_t* pre, const uint4* topo,
+                         const uint2* ends, const WalkNode* wn, int64_t nn, uint8_t* level, uint32_t* first,
+                         uint32_t* count, double* com, double* mass, hipStream_t s)
 {
-    if (n == 0) return;
-    k_emit<<<grid_for(n, 256), 256, 0, s>>>(skeys, c, pre, n, level, first, count, next, octant);
-}
-
-void launch_count_children(const uint8_t* level, const uint32_t* count, const uint32_t* next, int64_t nn,
-                           uint32_t* nchild, hipStream_t s)
-{
-    if (nn == 0) return;
-    k_count_children<<<grid_for(nn, 256), 256, 0, s>>>(level, count, next, nn, nchild);
-}
-
-void launch_bfs_order(const uint8_t* level, int64_t nn, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1,
-                      void* sort_temp, uint32_t* bfs, uint32_t** bfs_to_pre, hipStream_t s)
-{
-    if (nn == 0) return;
-    k_level_keys<<<grid_for(nn, 256), 256, 0, s>>>(level, nn, k0, v0);
-    uint64_t* ko;
-    radix_sort_pairs(k0, v0, k1, v1, nn, 8, sort_temp, s, &ko, bfs_to_pre);
-    k_bfs_scatter<<<grid_for(nn, 256), 256, 0, s>>>(*bfs_to_pre, nn, bfs);
+    k_preorder<<<grid_for(n, kTreeThreads), kTreeThreads, 0, s>>>(skeys, n, table, pre);
+    k_export_nodes<<<grid_for(nn, 256), 256, 0, s>>>(skeys, n, pre, topo, ends, wn, nn, level, first, count, com, mass);
 }
 
 }  // namespace tc

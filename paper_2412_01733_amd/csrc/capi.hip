@@ -4,6 +4,7 @@
 
 #include <cmath>
 #include <cstdarg>
+#include <cstddef>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -55,15 +56,16 @@ enum Stage { kStKeys = 0, kStSort, kStTree, kStMoments, kStWalk, kStDiag, kStBwd
 
 struct HostMirror {
     Geom geom;
-    uint32_t level_hist[kLevels + 2];
-    uint32_t total;
+    uint32_t level_hist[kTreeRows];  // read back with geom in one copy
     uint32_t level_off[kLevels + 1];
     double diag[4];
+    uint32_t status;                 // read back with diag in one copy
     unsigned long long inter;
     unsigned long long visits[kNumVisitCounters];
     double step[10];
-    uint32_t status;
 };
+static_assert(offsetof(HostMirror, level_hist) == sizeof(Geom) && offsetof(HostMirror, status) == offsetof(HostMirror, diag) + 32,
+              "read back together");
 
 }  // namespace
 
@@ -78,17 +80,16 @@ struct tc_tree {
     tc_dtype dtype = TC_F32;
 
     // particle-sized
-    Buf keys0, keys1, vals0, vals1, rec, sp, c, cnt, pre, sorted_counts, diag_part;
+    Buf keys0, keys1, vals0, vals1, rec, sp, leaf_of, sorted_counts, diag_part;
     uint64_t* skeys = nullptr;
     uint32_t* perm = nullptr;
-    Buf sort_temp, scan_temp, bounds_part;
+    Buf sort_temp, tree_table, bounds_part;
     // node-sized
-    Buf level, first, count, next, nchild, bfs, nk0, nk1, nv0, nv1, node_sort_temp, wn, diag_temp, parent, octant;
-    Buf topo, nord, order;     // the walk's target order (particle-sized); dense topology and scratch (node-sized)
+    Buf topo, ends, up, wn, diag_temp;
+    Buf order;                 // the walk's target order (particle-sized)
     // adjoint and leapfrog
     Buf node_grad, uc, part_grad, target_grad, step_temp;
     Buf lists, list_len;       // stored interaction lists of the last tc_forces (TC_STORE_LISTS)
-    uint32_t* bfs_to_pre = nullptr;  // inside nv0 or nv1
     // small device block
     Buf small;
     Geom* geom = nullptr;
@@ -199,19 +200,20 @@ tc_status carve_small(tc_tree* t, hipStream_t s)
 {
     TC_TRY(ensure(t, t->small, 1024, s));
     char* p = (char*)t->small.p;
-    t->geom = (Geom*)p;
-    p += (sizeof(Geom) + 15) & ~(size_t)15;
+    t->geom = (Geom*)p;          // geom and level_hist, and diag_out and status, are read back together
+    p += sizeof(Geom);
+    t->level_hist = (uint32_t*)p;
+    p += 4 * kTreeRows;
+    static_assert((sizeof(Geom) + 4 * kTreeRows) % 16 == 0, "alignment of what follows");
     t->diag_out = (double*)p;
     p += 4 * sizeof(double);
+    t->status = (uint32_t*)p;
+    p += 16;
     t->step_out = (double*)p;
     p += 10 * sizeof(double);
     t->inter_total = (unsigned long long*)p;
     p += 8;
     t->visits = (unsigned long long*)p;
-    p += 8 * kNumVisitCounters;
-    t->level_hist = (uint32_t*)p;
-    p += 4 * (kLevels + 2);
-    t->status = (uint32_t*)p;
     return TC_OK;
 }
 
@@ -291,7 +293,7 @@ tc_status build_impl(tc_tree* t, const void* pos, const void* mass, int64_t n, t
     t->build_pending = false;
     t->counted = false;
     t->lists_stored = false;
-    for (int l = 0; l < kLevels + 2; ++l) t->host->level_hist[l] = 0;
+    for (int l = 0; l < kTreeRows; ++l) t->host->level_hist[l] = 0;
     if (n == 0) {
         Geom g{};
         g.L = 1.0;
@@ -306,37 +308,38 @@ tc_status build_impl(tc_tree* t, const void* pos, const void* mass, int64_t n, t
     TC_TRY(ensure(t, t->keys1, n8, s));
     TC_TRY(ensure(t, t->vals0, n4, s));
     TC_TRY(ensure(t, t->vals1, n4, s));
-    TC_TRY(ensure(t, t->rec, record_bytes(n, dt), s));
     TC_TRY(ensure(t, t->sp, (size_t)n * sizeof(Particle), s));
-    TC_TRY(ensure(t, t->c, (size_t)n, s));
-    TC_TRY(ensure(t, t->cnt, n4, s));
-    TC_TRY(ensure(t, t->pre, n4 + 8, s));
-    TC_TRY(ensure(t, t->sort_temp, radix_temp_bytes(n), s));
-    TC_TRY(ensure(t, t->scan_temp, scan_temp_bytes(n), s));
-    const int nb = bounds_blocks(n);
+    TC_TRY(ensure(t, t->leaf_of, n4, s));
+    TC_TRY(ensure(t, t->tree_table, tree_table_bytes(n), s));
+    const bool small = n <= kSortSmall;
+    const int nb = small && sort_small_lone(n) ? 0 : bounds_blocks(n);
     TC_TRY(ensure(t, t->bounds_part, (size_t)nb * 8 * sizeof(double), s));
+    if (!small) {
+        TC_TRY(ensure(t, t->rec, record_bytes(n, dt), s));
+        TC_TRY(ensure(t, t->sort_temp, radix_temp_bytes(n), s));
+    }
 
     stage_begin(t, kStKeys, s);
-    launch_bounds(pos, mass, n, dt, P<double>(t->bounds_part), nb, t->geom, s);
-    launch_keys(pos, mass, n, dt, t->geom, P<uint64_t>(t->keys0), P<uint32_t>(t->vals0), t->rec.p, s);
+    if (nb > 0) launch_bounds(pos, mass, n, dt, P<double>(t->bounds_part), nb, small ? nullptr : t->geom, s);
+    if (!small) launch_keys(pos, mass, n, dt, t->geom, P<uint64_t>(t->keys0), P<uint32_t>(t->vals0), t->rec.p, s);
     stage_end(t, kStKeys, s);
     TC_TRY(check_launch("keys"));
 
     stage_begin(t, kStSort, s);
-    radix_sort_pairs(P<uint64_t>(t->keys0), P<uint32_t>(t->vals0), P<uint64_t>(t->keys1), P<uint32_t>(t->vals1),
-                     n, 63, t->sort_temp.p, s, &t->skeys, &t->perm);
-    launch_gather(t->rec.p, n, dt, t->perm, P<Particle>(t->sp), s);
+    if (small) {
+        launch_sort_small(pos, mass, n, dt, P<double>(t->bounds_part), nb, t->geom, P<uint64_t>(t->keys0), P<uint32_t>(t->vals0),
+                          P<uint64_t>(t->keys1), P<uint32_t>(t->vals1), P<Particle>(t->sp), s, &t->skeys, &t->perm);
+    } else {
+        radix_sort_pairs(P<uint64_t>(t->keys0), P<uint32_t>(t->vals0), P<uint64_t>(t->keys1), P<uint32_t>(t->vals1),
+                         n, 63, t->sort_temp.p, s, &t->skeys, &t->perm);
+        launch_gather(t->rec.p, n, dt, t->perm, P<Particle>(t->sp), s);
+    }
     stage_end(t, kStSort, s);
     TC_TRY(check_launch("sort"));
 
     stage_begin(t, kStTree, s);
-    launch_adjacent_levels(t->skeys, n, P<int8_t>(t->c), s);
-    launch_fill_u32(t->level_hist, kLevels + 2, 0u, s);
-    launch_node_counts(P<int8_t>(t->c), n, P<uint32_t>(t->cnt), t->level_hist, s);
-    launch_exclusive_scan_u32(P<uint32_t>(t->cnt), P<uint32_t>(t->pre), n, t->scan_temp.p, s);
-    HIP_TRY(hipMemcpyAsync(&t->host->geom, t->geom, sizeof(Geom), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(t->host->level_hist, t->level_hist, 4 * (kLevels + 2), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&t->host->total, P<uint32_t>(t->pre) + n, 4, hipMemcpyDeviceToHost, s));
+    launch_tree_counts(t->skeys, n, P<uint32_t>(t->tree_table), t->level_hist, s);
+    HIP_TRY(hipMemcpyAsync(&t->host->geom, t->geom, sizeof(Geom) + 4 * kTreeRows, hipMemcpyDeviceToHost, s));
     TC_TRY(check_launch("tree counts"));
     HIP_TRY(hipStreamSynchronize(s));
     // the previous walk on this handle, enqueued before this build on the same stream, is complete
@@ -352,34 +355,14 @@ tc_status build_impl(tc_tree* t, const void* pos, const void* mass, int64_t n, t
     if (total >= 0xFFFFFFFFull) return fail(TC_ERR_OVERFLOW, "octree needs %llu nodes (limit 2^32 - 1)",
                                            (unsigned long long)total);
     t->host->level_off[kLevels] = (uint32_t)total;
-    if (total != t->host->total) return fail(TC_ERR_DEVICE, "node count mismatch (%llu vs %u)",
-                                             (unsigned long long)total, t->host->total);
     const int64_t nn = (int64_t)total;
     t->nn = nn;
-    const size_t m4 = (size_t)nn * 4;
-    TC_TRY(ensure(t, t->level, (size_t)nn, s));
-    TC_TRY(ensure(t, t->octant, (size_t)nn, s));
-    TC_TRY(ensure(t, t->first, m4, s));
-    TC_TRY(ensure(t, t->count, m4, s));
-    TC_TRY(ensure(t, t->next, m4, s));
-    TC_TRY(ensure(t, t->nchild, m4, s));
-    TC_TRY(ensure(t, t->bfs, m4, s));
-    TC_TRY(ensure(t, t->nk0, (size_t)nn * 8, s));
-    TC_TRY(ensure(t, t->nk1, (size_t)nn * 8, s));
-    TC_TRY(ensure(t, t->nv0, m4, s));
-    TC_TRY(ensure(t, t->nv1, m4, s));
-    TC_TRY(ensure(t, t->node_sort_temp, radix_temp_bytes(nn), s));
+    TC_TRY(ensure(t, t->topo, (size_t)nn * sizeof(uint4), s));
+    TC_TRY(ensure(t, t->ends, (size_t)nn * sizeof(uint2), s));
     TC_TRY(ensure(t, t->wn, (size_t)nn * sizeof(WalkNode), s));
-    TC_TRY(ensure(t, t->parent, m4, s));
-    TC_TRY(ensure(t, t->topo, (size_t)nn * 16, s));
 
-    launch_fill_u32(t->status, 1, 0u, s);  // status bits stay set until the next build
-    launch_emit_nodes(t->skeys, P<int8_t>(t->c), P<uint32_t>(t->pre), n, P<uint8_t>(t->level), P<uint32_t>(t->first),
-                      P<uint32_t>(t->count), P<uint32_t>(t->next), P<uint8_t>(t->octant), s);
-    launch_count_children(P<uint8_t>(t->level), P<uint32_t>(t->count), P<uint32_t>(t->next), nn,
-                          P<uint32_t>(t->nchild), s);
-    launch_bfs_order(P<uint8_t>(t->level), nn, P<uint64_t>(t->nk0), P<uint32_t>(t->nv0), P<uint64_t>(t->nk1),
-                     P<uint32_t>(t->nv1), t->node_sort_temp.p, P<uint32_t>(t->bfs), &t->bfs_to_pre, s);
+    launch_emit(t->skeys, n, P<uint32_t>(t->tree_table), t->host->level_off, P<Particle>(t->sp), P<uint4>(t->topo),
+                P<uint2>(t->ends), P<WalkNode>(t->wn), P<uint32_t>(t->leaf_of), t->status, s);
     stage_end(t, kStTree, s);
     TC_TRY(check_launch("tree"));
     t->state = 1;
@@ -390,12 +373,12 @@ tc_status moments_impl(tc_tree* t, hipStream_t s)
 {
     if (t->n > 0) {
         stage_begin(t, kStMoments, s);
-        launch_moments(t->host->level_off, t->bfs_to_pre, P<uint32_t>(t->bfs), P<uint32_t>(t->first),
-                       P<uint32_t>(t->count), P<uint32_t>(t->nchild), t->skeys, P<uint8_t>(t->octant), P<Particle>(t->sp), t->geom,
-                       P<WalkNode>(t->wn), P<uint32_t>(t->parent), P<uint4>(t->topo), s);
-        TC_TRY(ensure(t, t->nord, (size_t)t->nn * sizeof(uint2), s));
+        TC_TRY(ensure(t, t->up, (size_t)t->nn * sizeof(uint2), s));
         TC_TRY(ensure(t, t->order, (size_t)t->n * 4, s));
-        launch_target_order(t->host->level_off, P<uint4>(t->topo), P<uint2>(t->nord), P<uint32_t>(t->order), s);
+        launch_moments(t->host->level_off, P<uint4>(t->topo), P<uint2>(t->ends), t->skeys, P<Particle>(t->sp), t->geom,
+                       P<WalkNode>(t->wn), s);
+        launch_target_order(t->n, t->nn, t->skeys, P<uint4>(t->topo), P<uint2>(t->ends), P<uint32_t>(t->leaf_of),
+                            P<uint2>(t->up), P<uint32_t>(t->order), s);
         stage_end(t, kStMoments, s);
         TC_TRY(check_launch("moments"));
     }
@@ -477,8 +460,7 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
     if (t->counted) launch_sum_counts(P<uint32_t>(t->sorted_counts), n, t->inter_total, s);
     stage_end(t, kStDiag, s);
     TC_TRY(check_launch("diagnostics"));
-    HIP_TRY(hipMemcpyAsync(t->host->diag, t->diag_out, 4 * sizeof(double), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(&t->host->status, t->status, 4, hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(t->host->diag, t->diag_out, 4 * sizeof(double) + 4, hipMemcpyDeviceToHost, s));
     t->walk_status_pending = true;
     if (t->counted) {
         HIP_TRY(hipMemcpyAsync(&t->host->inter, t->inter_total, 8, hipMemcpyDeviceToHost, s));
@@ -523,7 +505,7 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     HIP_TRY(hipMemcpyAsync(&t->host->status, t->status, 4, hipMemcpyDeviceToHost, s));
     t->walk_status_pending = true;
     stage_begin(t, kStBwdDown, s);
-    launch_adjoint_down(t->host->level_off, P<WalkNode>(t->wn), P<uint32_t>(t->parent), a.node_grad, P<double>(t->uc),
+    launch_adjoint_down(t->host->level_off, P<WalkNode>(t->wn), P<uint2>(t->up), a.node_grad, P<double>(t->uc),
                         a.sp, t->perm, a.target_grad, a.part_grad, g_pos, g_mass,
                         t->last_mode == TC_WALK_F64, s);
     stage_end(t, kStBwdDown, s);
@@ -852,7 +834,7 @@ tc_status tc_tree_export(const tc_tree* t, uint64_t* keys, uint32_t* perm, uint8
     if ((com || mass) && !(t->state & 2u)) return fail(TC_ERR_STATE, "tc_tree_export: com/mass need tc_moments");
     TC_TRY(check_device(t));
     hipStream_t s = (hipStream_t)stream;
-    const size_t n = (size_t)t->n, nn = (size_t)t->nn;
+    const size_t n = (size_t)t->n;
     if (n == 0) return TC_OK;
     auto cp = [&](void* dst, const void* src, size_t bytes) -> tc_status {
         if (!dst) return TC_OK;
@@ -861,11 +843,11 @@ tc_status tc_tree_export(const tc_tree* t, uint64_t* keys, uint32_t* perm, uint8
     };
     TC_TRY(cp(keys, t->skeys, n * 8));
     TC_TRY(cp(perm, t->perm, n * 4));
-    TC_TRY(cp(level, t->level.p, nn));
-    TC_TRY(cp(first, t->first.p, nn * 4));
-    TC_TRY(cp(count, t->count.p, nn * 4));
-    if (com || mass) {
-        launch_export_moments(P<WalkNode>(t->wn), P<uint32_t>(t->bfs), (int64_t)nn, com, mass, s);
+    if (level || first || count || com || mass) {
+        // the sort's spare key buffer holds the pre-order numbers meanwhile
+        uint32_t* pre = (uint32_t*)(t->skeys == P<uint64_t>(t->keys0) ? t->keys1.p : t->keys0.p);
+        launch_export_nodes(t->skeys, t->n, P<uint32_t>(t->tree_table), pre, P<uint4>(t->topo), P<uint2>(t->ends),
+                            P<WalkNode>(t->wn), t->nn, level, first, count, com, mass, s);
         TC_TRY(check_launch("export"));
     }
     return mark_done(const_cast<tc_tree*>(t), s, TC_OK);
@@ -897,11 +879,10 @@ void tc_tree_free(tc_tree* t)
     if (!t) return;
     // wait for the work the handle's calls enqueued (on whichever stream), not the whole device
     if (t->done && hipEventSynchronize(t->done) != hipSuccess) (void)hipGetLastError();
-    Buf* bufs[] = {&t->keys0, &t->keys1, &t->vals0, &t->vals1, &t->rec, &t->sp, &t->c, &t->cnt,
-                   &t->pre, &t->sorted_counts, &t->diag_part, &t->sort_temp, &t->scan_temp, &t->bounds_part,
-                   &t->level, &t->first, &t->count, &t->next, &t->nchild, &t->bfs, &t->nk0, &t->nk1,
-                   &t->nv0, &t->nv1, &t->node_sort_temp, &t->wn, &t->diag_temp, &t->parent, &t->topo, &t->nord, &t->order, &t->octant, &t->node_grad,
-                   &t->uc, &t->part_grad, &t->target_grad, &t->step_temp, &t->lists, &t->list_len, &t->small};
+    Buf* bufs[] = {&t->keys0, &t->keys1, &t->vals0, &t->vals1, &t->rec, &t->sp, &t->leaf_of, &t->sorted_counts,
+                   &t->diag_part, &t->sort_temp, &t->tree_table, &t->bounds_part, &t->topo, &t->ends, &t->up, &t->wn,
+                   &t->diag_temp, &t->order, &t->node_grad, &t->uc, &t->part_grad, &t->target_grad, &t->step_temp,
+                   &t->lists, &t->list_len, &t->small};
     for (Buf* b : bufs) release(t, *b);
     for (auto& e : t->ev)
         if (e) (void)hipEventDestroy(e);

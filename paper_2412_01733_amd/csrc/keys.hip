@@ -9,10 +9,7 @@
 //   key = interleave(q_x, q_y, q_z), x bit highest in every triple.
 // All arithmetic here is FP64 (FP32 inputs are widened exactly) with no FMA
 // contraction (the library is compiled with -ffp-contract=off).
-#include <float.h>
-#include <math.h>
-
-#include "tc_internal.h"
+#include "keys_common.h"
 
 namespace tc {
 namespace {
@@ -25,51 +22,31 @@ __global__ __launch_bounds__(kBoundsThreads) void k_bounds_partial(const T* __re
                                                                    int64_t n,
                                                                    double* __restrict__ part)
 {
-    double mn[3] = {DBL_MAX, DBL_MAX, DBL_MAX};
-    double mx[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
+    double mm[6] = {DBL_MAX, DBL_MAX, DBL_MAX, -DBL_MAX, -DBL_MAX, -DBL_MAX};
     uint32_t bad = 0;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            double x = (double)pos[3 * i + k];
-            if (!isfinite(x)) {
-                bad |= 1u;
-            } else {
-                mn[k] = fmin(mn[k], x);
-                mx[k] = fmax(mx[k], x);
-            }
-        }
-        double m = (double)mass[i];
-        if (!(m >= 0.0) || !isfinite(m)) bad |= 2u;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        bounds_add(pos, mass, i, mm, bad);
+    bounds_wave(mm, bad);
+    __shared__ double red[kBoundsThreads / 64][8];
+    if ((threadIdx.x & 63) == 0) {
+        for (int k = 0; k < 6; ++k) red[threadIdx.x >> 6][k] = mm[k];
+        red[threadIdx.x >> 6][6] = (double)bad;
     }
-    __shared__ double red[6][kBoundsThreads];
-    __shared__ uint32_t redbad[kBoundsThreads];
-    for (int k = 0; k < 3; ++k) {
-        red[k][threadIdx.x] = mn[k];
-        red[3 + k][threadIdx.x] = mx[k];
-    }
-    redbad[threadIdx.x] = bad;
     __syncthreads();
-    for (int o = kBoundsThreads / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            for (int k = 0; k < 3; ++k) {
-                red[k][threadIdx.x] = fmin(red[k][threadIdx.x], red[k][threadIdx.x + o]);
-                red[3 + k][threadIdx.x] = fmax(red[3 + k][threadIdx.x], red[3 + k][threadIdx.x + o]);
-            }
-            redbad[threadIdx.x] |= redbad[threadIdx.x + o];
+    if (threadIdx.x < 7) {
+        const int k = threadIdx.x;
+        double v = red[0][k];
+        for (int w = 1; w < kBoundsThreads / 64; ++w) {
+            const double u = red[w][k];
+            v = k < 3 ? fmin(v, u) : k < 6 ? fmax(v, u) : (double)((uint32_t)v | (uint32_t)u);
         }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        for (int k = 0; k < 6; ++k) part[8 * blockIdx.x + k] = red[k][0];
-        part[8 * blockIdx.x + 6] = (double)redbad[0];
-        part[8 * blockIdx.x + 7] = 0.0;
+        part[8 * blockIdx.x + k] = v;
     }
 }
 
 __global__ __launch_bounds__(kBoundsThreads) void k_bounds_final(const double* __restrict__ part,
-                                                                 int nblocks, int64_t n,
+                                                                 int nblocks,
                                                                  Geom* __restrict__ g)
 {
     __shared__ double red[6][kBoundsThreads];
@@ -100,51 +77,11 @@ __global__ __launch_bounds__(kBoundsThreads) void k_bounds_final(const double* _
         }
         __syncthreads();
     }
-    if (threadIdx.x != 0) return;
-    double E = 0.0;
-    for (int k = 0; k < 3; ++k) {
-        double lo = n > 0 ? red[k][0] : 0.0;
-        double hi = n > 0 ? red[3 + k][0] : 0.0;
-        g->lo[k] = lo;
-        double ext = hi - lo;
-        if (ext > E) E = ext;
+    if (threadIdx.x == 0) {
+        double mm[6];
+        for (int k = 0; k < 6; ++k) mm[k] = red[k][0];
+        *g = make_geom(mm, redbad[0]);
     }
-    uint32_t b = redbad[0];
-    int eL = 0;
-    if (!isfinite(E)) {
-        b |= 1u;
-    } else if (E > 0.0) {
-        // E = f 2^e, f in [0.5, 1): a power of two iff f == 0.5
-        int e;
-        double f = frexp(E, &e);
-        eL = (f == 0.5) ? e - 1 : e;
-    }
-    g->log2L = eL;
-    g->L = ldexp(1.0, eL);
-    g->scale = ldexp(1.0, 21 - eL);
-    g->h = ldexp(1.0, eL - 21);
-    g->bad = b;
-    g->nnodes = 0;
-}
-
-// Spread the low 21 bits of v so that bit b lands on bit 3b.
-__device__ inline uint64_t spread3(uint64_t v)
-{
-    v &= 0x1FFFFFull;
-    v = (v | (v << 32)) & 0x001F00000000FFFFull;
-    v = (v | (v << 16)) & 0x001F0000FF0000FFull;
-    v = (v | (v << 8)) & 0x100F00F00F00F00Full;
-    v = (v | (v << 4)) & 0x10C30C30C30C30C3ull;
-    v = (v | (v << 2)) & 0x1249249249249249ull;
-    return v;
-}
-
-__device__ inline uint64_t quantise(double x, double lo, double scale)
-{
-    double f = floor((x - lo) * scale);
-    if (!(f >= 0.0)) f = 0.0;
-    if (f > (double)kQMax) return kQMax;
-    return (uint64_t)f;
 }
 
 // Packed particle record {x, y, z, m} in caller order, so that the gather
@@ -189,7 +126,7 @@ __global__ __launch_bounds__(256) void k_keys(const T* __restrict__ pos, const T
     uint64_t qx = quantise((double)x, g->lo[0], sc);
     uint64_t qy = quantise((double)y, g->lo[1], sc);
     uint64_t qz = quantise((double)z, g->lo[2], sc);
-    keys[i] = (spread3(qx) << 2) | (spread3(qy) << 1) | spread3(qz);
+    keys[i] = morton(qx, qy, qz);
     idx[i] = (uint32_t)i;
     Rec<T>::put(rec, i, x, y, z, mass[i]);
 }
@@ -228,7 +165,7 @@ void launch_bounds(const void* pos, const void* mass, int64_t n, tc_dtype dt, do
     else
         k_bounds_partial<double><<<nblocks, kBoundsThreads, 0, s>>>((const double*)pos,
                                                                     (const double*)mass, n, partials);
-    k_bounds_final<<<1, kBoundsThreads, 0, s>>>(partials, nblocks, n, geom);
+    if (geom) k_bounds_final<<<1, kBoundsThreads, 0, s>>>(partials, nblocks, geom);
 }
 
 size_t record_bytes(int64_t n, tc_dtype dt) { return (size_t)n * 4 * (dt == TC_F32 ? sizeof(float) : sizeof(double)); }

@@ -38,48 +38,27 @@ __device__ inline void cell_centre(uint64_t key, int level, const Geom* g, doubl
     }
 }
 
-// One node, at breadth-first position b (pre-order index p).
-__device__ inline void moments_node(int64_t b, int l, const uint32_t* __restrict__ bfs_to_pre,
-                                    const uint32_t* __restrict__ bfs, const uint32_t* __restrict__ first,
-                                    const uint32_t* __restrict__ count, const uint32_t* __restrict__ nchild,
-                                    const uint64_t* __restrict__ skeys, const uint8_t* __restrict__ octant,
-                                    const Particle* __restrict__ sp,
-                                    const Geom* __restrict__ g, WalkNode* __restrict__ wn,
-                                    uint32_t* __restrict__ parent, uint4* __restrict__ topo)
+// Node b.  One-particle leaves are complete already (k_emit).
+__device__ inline void moments_node(int64_t b, int l, const uint4* __restrict__ topo, const uint2* __restrict__ ends,
+                                    const uint64_t* __restrict__ skeys, const Particle* __restrict__ sp,
+                                    const Geom* __restrict__ g, WalkNode* __restrict__ wn)
 {
-    const uint32_t p = bfs_to_pre[b];
-    const uint32_t f = first[p], c = count[p], nc = nchild[p];
-    double M = 0.0, X[3];
-    bool centre = false;
-    uint32_t child = 0;
+    const uint4 rec = topo[b];  // first, child, meta
+    if (meta_single(rec.z)) return;
+    const uint2 en = ends[b];   // end, last child
+    const uint32_t f = rec.x, c = en.x - f, child = rec.y;
+    const uint32_t nc = meta_leaf(rec.z) ? 0u : en.y - child + 1u;
+    double M = 0.0, S0 = 0.0, S1 = 0.0, S2 = 0.0, X[3];
     if (nc == 0) {
-        if (c == 1) {
-            const Particle q = sp[f];
-            M = q.m;
-            X[0] = q.x;
-            X[1] = q.y;
-            X[2] = q.z;
-        } else {
-            double S0 = 0.0, S1 = 0.0, S2 = 0.0;
-            for (uint32_t j = f; j < f + c; ++j) {
-                const Particle q = sp[j];
-                M += q.m;
-                S0 += q.m * q.x;
-                S1 += q.m * q.y;
-                S2 += q.m * q.z;
-            }
-            if (M == 0.0) centre = true;
-            else {
-                X[0] = S0 / M;
-                X[1] = S1 / M;
-                X[2] = S2 / M;
-            }
+        for (uint32_t j = f; j < f + c; ++j) {
+            const Particle q = sp[j];
+            M += q.m;
+            S0 += q.m * q.x;
+            S1 += q.m * q.y;
+            S2 += q.m * q.z;
         }
     } else {
-        child = bfs[p + 1];  // the first child follows its parent in pre-order
-        double S0 = 0.0, S1 = 0.0, S2 = 0.0;
         for (uint32_t k = 0; k < nc; ++k) {
-            parent[child + k] = (uint32_t)b;
             const double2 xy = *reinterpret_cast<const double2*>(&wn[child + k].x);
             const double2 zm = *reinterpret_cast<const double2*>(&wn[child + k].z);
             const double mc = zm.y;
@@ -88,31 +67,24 @@ __device__ inline void moments_node(int64_t b, int l, const uint32_t* __restrict
             S1 += mc * xy.y;
             S2 += mc * zm.x;
         }
-        if (M == 0.0) centre = true;
-        else {
-            X[0] = S0 / M;
-            X[1] = S1 / M;
-            X[2] = S2 / M;
-        }
     }
-    if (centre) cell_centre(skeys[f], l, g, X);
-    const bool single = nc == 0 && c == 1;
-    const uint32_t oc = octant[p];
-    const uint32_t meta = nc | ((uint32_t)l << 8) | (single ? (1u << 13) : 0u) | (nc == 0 ? (1u << 16) : 0u) |
-                          (single ? (1u << 17) : 0u) | (oc << 18);
+    if (M == 0.0) {
+        cell_centre(skeys[f], l, g, X);
+    } else {
+        X[0] = S0 / M;
+        X[1] = S1 / M;
+        X[2] = S2 / M;
+    }
     uint4* o = reinterpret_cast<uint4*>(wn + b);
     o[0] = make_uint4(__double2loint(X[0]), __double2hiint(X[0]), __double2loint(X[1]), __double2hiint(X[1]));
     o[1] = make_uint4(__double2loint(X[2]), __double2hiint(X[2]), __double2loint(M), __double2hiint(M));
-    o[2] = make_uint4(f, c, child, meta);
-    topo[b] = make_uint4(f, c, child, meta);  // the same topology half, densely, for the target-order pass
+    o[2] = make_uint4(f, c, child, rec.z | nc);
 }
 
-#define MOM_ARGS                                                                                                  \
-    const uint32_t *__restrict__ bfs_to_pre, const uint32_t *__restrict__ bfs, const uint32_t *__restrict__ first, \
-        const uint32_t *__restrict__ count, const uint32_t *__restrict__ nchild, const uint64_t *__restrict__ skeys, \
-        const uint8_t *__restrict__ octant, const Particle *__restrict__ sp, const Geom *__restrict__ g, WalkNode *__restrict__ wn,                  \
-        uint32_t *__restrict__ parent, uint4 *__restrict__ topo
-#define MOM_PASS bfs_to_pre, bfs, first, count, nchild, skeys, octant, sp, g, wn, parent, topo
+#define MOM_ARGS                                                                                               \
+    const uint4 *__restrict__ topo, const uint2 *__restrict__ ends, const uint64_t *__restrict__ skeys,        \
+        const Particle *__restrict__ sp, const Geom *__restrict__ g, WalkNode *__restrict__ wn
+#define MOM_PASS topo, ends, skeys, sp, g, wn
 
 // One level with many nodes: one thread per node.
 __global__ __launch_bounds__(256) void k_moments_level(int l, uint32_t b0, uint32_t b1, MOM_ARGS)
@@ -135,27 +107,10 @@ __global__ __launch_bounds__(kSmallLevelThreads) void k_moments_small(int lhi, i
     }
 }
 
-__global__ __launch_bounds__(256) void k_export_moments(const WalkNode* __restrict__ wn,
-                                                        const uint32_t* __restrict__ bfs, int64_t nn,
-                                                        double* __restrict__ com, double* __restrict__ mass)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nn) return;
-    const WalkNode r = wn[bfs[p]];
-    if (com) {
-        com[3 * p + 0] = r.x;
-        com[3 * p + 1] = r.y;
-        com[3 * p + 2] = r.z;
-    }
-    if (mass) mass[p] = r.m;
-}
-
 }  // namespace
 
-void launch_moments(const uint32_t* level_off_host, const uint32_t* bfs_to_pre, const uint32_t* bfs,
-                    const uint32_t* first, const uint32_t* count, const uint32_t* nchild, const uint64_t* skeys,
-                    const uint8_t* octant, const Particle* sp, const Geom* g, WalkNode* wn, uint32_t* parent,
-                    uint4* topo, hipStream_t s)
+void launch_moments(const uint32_t* level_off_host, const uint4* topo, const uint2* ends, const uint64_t* skeys,
+                    const Particle* sp, const Geom* g, WalkNode* wn, hipStream_t s)
 {
     LevelOffsets off;
     for (int l = 0; l <= kLevels; ++l) off.off[l] = level_off_host[l];
@@ -173,13 +128,6 @@ void launch_moments(const uint32_t* level_off_host, const uint32_t* bfs_to_pre, 
         k_moments_level<<<(unsigned)blocks, 256, 0, s>>>(l, off.off[l], off.off[l + 1], MOM_PASS);
         --l;
     }
-}
-
-void launch_export_moments(const WalkNode* wn, const uint32_t* bfs, int64_t nn, double* com, double* mass,
-                           hipStream_t s)
-{
-    if (nn == 0) return;
-    k_export_moments<<<(unsigned)((nn + 255) / 256), 256, 0, s>>>(wn, bfs, nn, com, mass);
 }
 
 }  // namespace tc

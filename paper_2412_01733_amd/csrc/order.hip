@@ -9,13 +9,15 @@
 // interaction set and terms are its own.
 //
 // Every octree cell is a contiguous range of the Hilbert order, just as it is
-// of the key order, so the order follows from the tree top-down (reading the
-// dense breadth-first topology records {first, count, child, meta}): a node's
-// particles start at its offset; its children follow each other in the order
-// of their Hilbert digits at their level (siblings share all higher digits);
-// a leaf lays out its particles in key order.  Level by level, root first
-// (one launch per populous level, one single-workgroup launch per run of
-// small levels).
+// of the key order: a node's children follow each other in the order of their
+// Hilbert digits at their level (siblings share all higher digits), and a leaf
+// lays out its particles in key order.  A child's distance from its parent's
+// start is the count of its siblings with lower digits; a particle's place is
+// the sum of these distances along its path.  The digits depend on the key
+// alone, so neither pass goes level by level: one thread per internal node steps
+// the state of the curve down the node's key and ranks the children, then one
+// thread per particle climbs to the root.  (0.29 ms at 1e7 particles and 55 us at
+// 1000, in 13 and 2 launches, when the offsets came down level by level.)
 //
 // Hilbert digits.  The index is that of the transposition algorithm of
 // J. Skilling, "Programming the Hilbert curve", AIP Conf. Proc. 707, 381
@@ -74,89 +76,71 @@ __device__ inline uint32_t hilbert_step(uint32_t st, uint32_t d, uint32_t* child
     return digit;
 }
 
-// Node b (breadth-first index): a leaf writes its particles' places in the
-// order; an internal node gives each child its offset and Hilbert state.
-// nord[b] = {offset, state} was written by the parent (the root starts at
-// offset 0 in the root state).
-__device__ inline void order_node(int64_t b, const uint4* __restrict__ topo, uint2* __restrict__ nord,
-                                  uint32_t* __restrict__ order)
+// Distances of an internal node's children from its start, with the link up:
+// up[child] = {distance, parent}.
+__global__ __launch_bounds__(256) void k_order_children(int64_t nn, const uint64_t* __restrict__ skeys,
+                                                        const uint4* __restrict__ topo, const uint2* __restrict__ ends,
+                                                        uint2* __restrict__ up)
 {
-    const uint4 rec = topo[b];  // first, count, child, meta
-    const uint2 me = b == 0 ? make_uint2(0u, kRootState) : nord[b];
-    if (meta_leaf(rec.w)) {
-        for (uint32_t j = 0; j < rec.y; ++j) order[me.x + j] = rec.x + j;
-        return;
-    }
-    const uint32_t nc = meta_nchild(rec.w) < 8u ? meta_nchild(rec.w) : 8u;
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= nn) return;
+    const uint4 rec = topo[b];  // first, child, meta
+    if (b == 0) up[0] = make_uint2(0u, 0u);
+    if (meta_leaf(rec.z)) return;
+    const uint64_t key = skeys[rec.x];
+    uint32_t st = kRootState;
+    for (int l = 1; l <= (int)meta_level(rec.z); ++l)
+        (void)hilbert_step(st, (uint32_t)(key >> (3 * (kMaxLevel - l))) & 7u, &st);
+    const uint32_t last = ends[b].y, nc = last - rec.y + 1u < 8u ? last - rec.y + 1u : 8u;
     // fixed-size, fully unrolled, so that the arrays stay in registers; an
     // absent child counts 0 and sorts last (digit 8)
-    uint32_t cnt[8], dig[8], cst[8];
+    uint32_t cnt[8], dig[8];
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
         cnt[k] = 0u;
         dig[k] = 8u;
-        cst[k] = 0u;
         if (k < nc) {
-            const uint4 c = topo[rec.z + k];
-            cnt[k] = c.y;
-            dig[k] = hilbert_step(me.y, meta_octant(c.w), &cst[k]);
+            const uint4 c = topo[rec.y + k];
+            uint32_t unused;
+            cnt[k] = meta_single(c.z) ? 1u : ends[rec.y + k].x - c.x;
+            dig[k] = hilbert_step(st, meta_octant(c.z), &unused);
         }
     }
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
         if (k < nc) {
-            uint32_t o = me.x;
+            uint32_t o = 0u;
 #pragma unroll
             for (uint32_t j = 0; j < 8; ++j)
                 if (dig[j] < dig[k]) o += cnt[j];
-            nord[rec.z + k] = make_uint2(o, cst[k]);
+            up[rec.y + k] = make_uint2(o, (uint32_t)b);
         }
     }
 }
 
-__global__ __launch_bounds__(256) void k_order_level(uint32_t b0, uint32_t b1, const uint4* __restrict__ topo,
-                                                     uint2* __restrict__ nord, uint32_t* __restrict__ order)
+__global__ __launch_bounds__(256) void k_order_place(int64_t n, const uint4* __restrict__ topo,
+                                                     const uint32_t* __restrict__ leaf_of, const uint2* __restrict__ up,
+                                                     uint32_t* __restrict__ order)
 {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t b = (int64_t)b0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; b < (int64_t)b1; b += stride)
-        order_node(b, topo, nord, order);
-}
-
-// A run of consecutive small levels [llo, lhi], root side first, in one
-// workgroup; a barrier separates the levels.
-__global__ __launch_bounds__(kSmallLevelThreads) void k_order_small(int llo, int lhi, LevelOffsets off,
-                                                                   const uint4* __restrict__ topo,
-                                                                   uint2* __restrict__ nord,
-                                                                   uint32_t* __restrict__ order)
-{
-    for (int l = llo; l <= lhi; ++l) {
-        for (int64_t b = (int64_t)off.off[l] + threadIdx.x; b < (int64_t)off.off[l + 1]; b += blockDim.x)
-            order_node(b, topo, nord, order);
-        __syncthreads();
+    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (s >= n) return;
+    uint32_t b = leaf_of[s];
+    uint32_t o = (uint32_t)s - topo[b].x;
+    for (int l = 0; l < kMaxLevel && b != 0u; ++l) {  // at most one step a level
+        const uint2 u = up[b];
+        o += u.x;
+        b = u.y;
     }
+    order[o] = (uint32_t)s;
 }
 
 }  // namespace
 
-void launch_target_order(const uint32_t* level_off_host, const uint4* topo, uint2* nord, uint32_t* order,
-                         hipStream_t s)
+void launch_target_order(int64_t n, int64_t nn, const uint64_t* skeys, const uint4* topo, const uint2* ends,
+                         const uint32_t* leaf_of, uint2* up, uint32_t* order, hipStream_t s)
 {
-    LevelOffsets off;
-    for (int l = 0; l <= kLevels; ++l) off.off[l] = level_off_host[l];
-    int l = 0;
-    while (l <= kMaxLevel) {
-        if (off.size(l) <= kSmallLevel) {
-            int hi = l;
-            while (hi < kMaxLevel && off.size(hi + 1) <= kSmallLevel) ++hi;
-            if (off.off[hi + 1] > off.off[l]) k_order_small<<<1, kSmallLevelThreads, 0, s>>>(l, hi, off, topo, nord, order);
-            l = hi + 1;
-            continue;
-        }
-        int64_t blocks = ((int64_t)off.size(l) + 255) / 256;
-        if (blocks > 8192) blocks = 8192;
-        k_order_level<<<(unsigned)blocks, 256, 0, s>>>(off.off[l], off.off[l + 1], topo, nord, order);
-        ++l;
-    }
+    k_order_children<<<(unsigned)((nn + 255) / 256), 256, 0, s>>>(nn, skeys, topo, ends, up);
+    k_order_place<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, topo, leaf_of, up, order);
 }
 
 }  // namespace tc

@@ -1,7 +1,8 @@
 // Stable LSD radix sort of (u64 key, u32 value) pairs, 8-bit digits.
 //
-// Each pass is reduce-then-scan: per-tile digit counts (digit-major table),
-// one exclusive scan of that table, then a stable scatter.  Within a tile the
+// Each pass is reduce-then-scan: per-tile digit counts (digit-major table), an
+// exclusive scan of each digit's row, then a stable scatter, whose blocks add up
+// the digit totals themselves.  Within a tile the
 // rank of an element among equal digits comes from 64-lane ballots (the peer
 // mask of lanes holding the same digit), accumulated wave by wave in LDS, so
 // element order inside every digit run is the input order: the sort is
@@ -76,6 +77,7 @@ __global__ __launch_bounds__(kSortThreads) void k_downsweep(const uint64_t* __re
                                                             uint32_t* __restrict__ vout, int64_t n,
                                                             int shift,
                                                             const uint32_t* __restrict__ offsets,
+                                                            const uint32_t* __restrict__ totals,
                                                             int64_t ntiles)
 {
     __shared__ uint32_t wcnt[kSortWaves][kRadix];
@@ -86,12 +88,26 @@ __global__ __launch_bounds__(kSortThreads) void k_downsweep(const uint64_t* __re
     __shared__ uint32_t sv[kSortTile];
 
     for (int j = threadIdx.x; j < kSortWaves * kRadix; j += kSortThreads) (&wcnt[0][0])[j] = 0;
-    for (int d = threadIdx.x; d < kRadix; d += kSortThreads)
-        gbase[d] = offsets[(int64_t)d * ntiles + blockIdx.x];
-    __syncthreads();
-
     const int w = threadIdx.x >> 6;
     const uint32_t lane = lane_id();
+    {
+        // first place of each digit: the totals of the digits below it, and of this digit's tiles before
+        // (kSortThreads == kRadix: one digit per thread)
+        const uint32_t tot = totals[threadIdx.x], off = offsets[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+        uint32_t v = tot;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(v, o, 64);
+            if ((int)lane >= o) v += u;
+        }
+        if (lane == 63) dsum[w] = v;
+        __syncthreads();
+        uint32_t below = 0;
+        for (int ww = 0; ww < w; ++ww) below += dsum[ww];
+        gbase[threadIdx.x] = below + v - tot + off;
+    }
+    __syncthreads();
+
     const int64_t tbase = (int64_t)blockIdx.x * kSortTile;
     const int64_t base = tbase + (int64_t)w * kWaveTile;
 
@@ -170,10 +186,8 @@ __global__ __launch_bounds__(kSortThreads) void k_downsweep(const uint64_t* __re
 
 size_t radix_temp_bytes(int64_t n)
 {
-    int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    int64_t m = ntiles * kRadix;
-    size_t b = (size_t)m * 4 * 2 + 8 + scan_temp_bytes(m);
-    return (b + 255) & ~(size_t)255;
+    const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
+    return ((size_t)(ntiles + 1) * kRadix * 4 + 255) & ~(size_t)255;
 }
 
 void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32_t* vals_alt, int64_t n,
@@ -182,19 +196,17 @@ void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32
     *keys_out = keys;
     *vals_out = vals;
     if (n <= 1) return;
-    int64_t ntiles = (n + kSortTile - 1) / kSortTile;
-    int64_t m = ntiles * kRadix;
+    const int64_t ntiles = (n + kSortTile - 1) / kSortTile;
     uint32_t* counts = (uint32_t*)temp;
-    uint32_t* offsets = counts + m;                 // m + 1 entries
-    void* stemp = (void*)(offsets + m + 2);
+    uint32_t* totals = counts + ntiles * kRadix;
     uint64_t* kin = keys;
     uint32_t* vin = vals;
     uint64_t* ko = keys_alt;
     uint32_t* vo = vals_alt;
     for (int shift = 0; shift < bits; shift += kRadixBits) {
         k_upsweep<<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, n, shift, counts, ntiles);
-        launch_exclusive_scan_u32(counts, offsets, m, stemp, s);
-        k_downsweep<<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, vin, ko, vo, n, shift, offsets, ntiles);
+        launch_scan_rows(counts, kRadix, ntiles, totals, s);
+        k_downsweep<<<(unsigned)ntiles, kSortThreads, 0, s>>>(kin, vin, ko, vo, n, shift, counts, totals, ntiles);
         uint64_t* tk = kin; kin = ko; ko = tk;
         uint32_t* tv = vin; vin = vo; vo = tv;
     }

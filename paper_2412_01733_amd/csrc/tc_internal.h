@@ -68,6 +68,7 @@ __host__ __device__ inline uint32_t meta_tau_index(uint32_t m) { return (m >> 8)
 // ---------------------------------------------------------------------------
 
 // keys.hip
+// (the partials only if geom is null)
 void launch_bounds(const void* pos, const void* mass, int64_t n, tc_dtype dt, double* partials,
                    int nblocks, Geom* geom, hipStream_t s);
 int bounds_blocks(int64_t n);
@@ -77,10 +78,8 @@ void launch_keys(const void* pos, const void* mass, int64_t n, tc_dtype dt, cons
                  uint32_t* idx, void* rec, hipStream_t s);
 void launch_gather(const void* rec, int64_t n, tc_dtype dt, const uint32_t* perm, Particle* sp, hipStream_t s);
 
-// scan.hip: exclusive scan, out[n] = total (out has n+1 entries)
-size_t scan_temp_bytes(int64_t n);
-void launch_exclusive_scan_u32(const uint32_t* in, uint32_t* out, int64_t n, void* temp,
-                               hipStream_t s);
+// scan.hip: exclusive scan of each row of a [rows, cols] table in place, its total in totals[row]
+void launch_scan_rows(uint32_t* table, int rows, int64_t cols, uint32_t* totals, hipStream_t s);
 
 // sort.hip: stable LSD radix sort of (u64 key, u32 value) pairs over the
 // low `bits` key bits.  Result ends in (keys_out, vals_out); the *_alt
@@ -90,30 +89,32 @@ void radix_sort_pairs(uint64_t* keys, uint32_t* vals, uint64_t* keys_alt, uint32
                       int64_t n, int bits, void* temp, hipStream_t s, uint64_t** keys_out,
                       uint32_t** vals_out);
 
-// build.hip
-void launch_adjacent_levels(const uint64_t* skeys, int64_t n, int8_t* c, hipStream_t s);
-// level_hist: [kLevels + 2] = nodes per level, leaves, multi-particle leaves
-void launch_node_counts(const int8_t* c, int64_t n, uint32_t* cnt, uint32_t* level_hist, hipStream_t s);
-void launch_emit_nodes(const uint64_t* skeys, const int8_t* c, const uint32_t* pre, int64_t n,
-                       uint8_t* level, uint32_t* first, uint32_t* count, uint32_t* next, uint8_t* octant,
-                       hipStream_t s);
-void launch_count_children(const uint8_t* level, const uint32_t* count, const uint32_t* next,
-                           int64_t nn, uint32_t* nchild, hipStream_t s);
-// Breadth-first order of the pre-order nodes (stable sort by level): writes
-// bfs[p] and points *bfs_to_pre at the inverse (inside v0 or v1).
-void launch_bfs_order(const uint8_t* level, int64_t nn, uint64_t* k0, uint32_t* v0, uint64_t* k1,
-                      uint32_t* v1, void* sort_temp, uint32_t* bfs, uint32_t** bfs_to_pre,
-                      hipStream_t s);
+// sort_small.hip: keys, sort and gather in one (kSortSmall: up to which n it is used).
+// part: the bounds' partials (nparts of them; none needed for a lone tile); writes geom.
+constexpr int64_t kSortSmall = 1 << 19;
+bool sort_small_lone(int64_t n);
+void launch_sort_small(const void* pos, const void* mass, int64_t n, tc_dtype dt, const double* part, int nparts,
+                       Geom* geom, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1, Particle* sp, hipStream_t s,
+                       uint64_t** keys_out, uint32_t** vals_out);
+
+// build.hip: the tree's rows of counts (nodes that begin, by level; leaves; multi-particle
+// leaves) per block of particles and in total, then the breadth-first node tables:
+// topo {first particle, first child, meta without nchild, 0}, ends {end, last child} (not for
+// one-particle leaves), the walk records of one-particle leaves, leaf_of[particle].
+constexpr int kTreeRows = kLevels + 2;
+size_t tree_table_bytes(int64_t n);
+void launch_tree_counts(const uint64_t* skeys, int64_t n, uint32_t* table, uint32_t* totals, hipStream_t s);
+void launch_emit(const uint64_t* skeys, int64_t n, const uint32_t* table, const uint32_t* level_off_host, const Particle* sp,
+                 uint4* topo, uint2* ends, WalkNode* wn, uint32_t* leaf_of, uint32_t* status, hipStream_t s);
+// Canonical export (pre-order); pre is scratch [n].  Any output may be null.
+void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table, uint32_t* pre, const uint4* topo,
+                         const uint2* ends, const WalkNode* wn, int64_t nn, uint8_t* level, uint32_t* first,
+                         uint32_t* count, double* com, double* mass, hipStream_t s);
 
 // moments.hip: one launch per level over the breadth-first ranges
 // [level_off_host[l], level_off_host[l+1]), deepest level first.
-void launch_moments(const uint32_t* level_off_host, const uint32_t* bfs_to_pre, const uint32_t* bfs,
-                    const uint32_t* first, const uint32_t* count, const uint32_t* nchild, const uint64_t* skeys,
-                    const uint8_t* octant, const Particle* sp, const Geom* geom, WalkNode* wn, uint32_t* parent,
-                    uint4* topo, hipStream_t s);
-// Canonical export: com/mass of pre-order node p from wn[bfs[p]].
-void launch_export_moments(const WalkNode* wn, const uint32_t* bfs, int64_t nn, double* com, double* mass,
-                           hipStream_t s);
+void launch_moments(const uint32_t* level_off_host, const uint4* topo, const uint2* ends, const uint64_t* skeys,
+                    const Particle* sp, const Geom* geom, WalkNode* wn, hipStream_t s);
 
 // walk.hip
 struct WalkArgs {
@@ -166,14 +167,13 @@ int adjoint_targets(int64_t n, tc_walk mode);
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
 void launch_walk_split_adjoint(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
 
-// order.hip: the walk's target order (Hilbert order of the particles), from
-// the breadth-first topology records {first, count, child, meta} (written
-// densely by the upward pass) top-down; nord is node-sized scratch.
-void launch_target_order(const uint32_t* level_off_host, const uint4* topo, uint2* nord, uint32_t* order,
-                         hipStream_t s);
+// order.hip: the walk's target order (Hilbert order of the particles); also
+// up[node] = {distance of the node from its parent's start in the order, parent}.
+void launch_target_order(int64_t n, int64_t nn, const uint64_t* skeys, const uint4* topo, const uint2* ends,
+                         const uint32_t* leaf_of, uint2* up, uint32_t* order, hipStream_t s);
 
 // adjoint.hip: top-down pass from node gradients to particle gradients.
-void launch_adjoint_down(const uint32_t* level_off_host, const WalkNode* wn, const uint32_t* parent,
+void launch_adjoint_down(const uint32_t* level_off_host, const WalkNode* wn, const uint2* up,
                          const double* node_grad, double* uc, const Particle* sp, const uint32_t* perm,
                          const double* target_grad,
                          const double* part_grad, void* g_pos, void* g_mass, bool out_f64, hipStream_t s);
