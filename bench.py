@@ -35,7 +35,7 @@ if ROOT not in sys.path:
 
 FLOPS_PER_INTERACTION = 20          # acc + pot, rsqrt counted as one
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_f32c_plummer1e7_traffic.txt")
-WALK_SRC = os.path.join(ROOT, "paper_2412_01733_amd", "csrc", "walk.hip")
+WALK_SRC = os.path.join(ROOT, "paper_2412_01733_amd", "csrc", "walk_forward.hip")
 BUILD_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "build_plummer1e7_traffic.md")
 BUILD_SRCS = ["keys.hip", "sort.hip", "scan.hip", "build.hip", "moments.hip", "order.hip"]
 PEAK_FP32_TFLOPS = 157.3             # MI355X FP32 vector (packed FMA)

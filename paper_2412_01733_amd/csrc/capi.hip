@@ -452,7 +452,8 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
     if (t->counted) launch_fill_u32((uint32_t*)t->visits, 2 * kNumVisitCounters, 0u, s);
     stage_begin(t, kStWalk, s);
     if (targets < 64) launch_walk_split(a, targets, mode, s);
-    else launch_walk(a, mode, t->counted, store, s);
+    else if (store) launch_walk(a, mode, t->counted, s);
+    else launch_walk_forward(a, mode, t->counted, s);
     stage_end(t, kStWalk, s);
     TC_TRY(check_launch("walk"));
     stage_begin(t, kStDiag, s);

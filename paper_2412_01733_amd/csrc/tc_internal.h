@@ -157,11 +157,14 @@ constexpr uint32_t kListCap = 8192;                     // records per wave (128
 constexpr uint32_t kListInvalid = 0xFFFFFFFFu;
 constexpr uint64_t kListMaxBytes = 4ull << 30;          // lists are stored only up to this size
 int64_t walk_waves(int64_t n);
-void launch_walk(const WalkArgs& a, tc_walk mode, bool count, bool store, hipStream_t s);
+// storing walk (with or without counting)
+void launch_walk(const WalkArgs& a, tc_walk mode, bool count, hipStream_t s);
+// walk_forward.hip: the walk that does not store
+void launch_walk_forward(const WalkArgs& a, tc_walk mode, bool count, hipStream_t s);
 void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 
 // walk_split.hip: the same walks with `targets` (8 or 16) targets a wavefront;
-// walk_targets / adjoint_targets: which to use for n particles (64: walk.hip)
+// walk_targets / adjoint_targets: which to use for n particles (64: walk_forward.hip, walk.hip)
 int walk_targets(int64_t n, tc_walk mode);
 int adjoint_targets(int64_t n, tc_walk mode);
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);

@@ -1,35 +1,15 @@
-// The Barnes-Hut walk: accelerations and potentials of Eq.(1) with the
-// opening rule of the TreeCode description (section 2).
+// The storing walk (TC_STORE_LISTS) and the adjoint walk (tc_forces_backward).
 //
-// Layout of the work.  One wavefront serves 64 consecutive targets of the
-// target order, the particles along the Hilbert curve (spatially compact; see
-// order.hip).  It walks the union of the 64 lanes' open sets
-// depth first: a stack in LDS holds groups of sibling nodes together with the
-// 64-bit mask of lanes that opened their parent.  Popping a group stages its
-// <= 8 children into LDS (one lane per child); every active lane then applies
-// the exact per-particle rule to each child:
-//   - the node contains the target           -> open (never accepted);
-//   - |X - x|^2 > (s_l / theta)^2            -> accept: one monopole term;
-//   - otherwise                              -> open.
-// A ballot of the opening lanes decides whether the child's own group is
-// pushed.  A one-particle leaf gives the same term whether accepted or
-// opened, so it is taken directly (self excluded); a multi-particle leaf
-// (several particles sharing a level-21 cell) that is opened contributes its
-// particles one by one.  The interaction sets are therefore exactly those of
-// the per-particle algorithm; only the summation order differs.
+// Both walk the tree for 64 consecutive targets of the target order a wavefront,
+// with the decisions of walk_forward.hip bit for bit (same anchor, same
+// operations, same box test), and act on every accepted node with the whole
+// wavefront: the storing walk records, in visit order, every (node, accepting
+// lanes) pair and every multi-particle leaf opened with its lanes; the adjoint
+// differentiates every term, the tree membership and the interaction sets held
+// fixed, and reduces the source side over the wavefront.
 //
-// Precision.  F32C: node and target coordinates enter as FP32 offsets from a
-// per-wave FP64 anchor (the first target of the wave), formed in FP64 once
-// per staged node, so differences stay small and accurate; interactions are
-// FP32 (hardware reciprocal square root); each group's partial sums are added
-// into per-lane Kahan-compensated totals.  F64: absolute FP64 coordinates,
-// FP64 reciprocal square root refined by one third-order correction, plain FP64
-// sums.  Both walks also reduce sum_i m_i a_i and sum_i m_i |a_i| in FP64,
-// one partial per wave, for the momentum diagnostic.
-//
-// The adjoint walk (tc_forces_backward) is the same kernel with ADJ = true:
-// it re-walks the tree with the same decisions and differentiates every
-// term, the tree membership and the interaction sets held fixed.
+// Precision: as in walk_forward.hip (F32C: FP32 offsets from the wave's FP64
+// anchor, Kahan-compensated totals; F64: FP64 throughout).
 #include <type_traits>
 
 #include "walk_common.h"
@@ -42,7 +22,7 @@ constexpr int kWalkThreads = 64 * kWalkWaves;
 constexpr uint32_t kXcdRun = 64;  // consecutive blocks one XCD takes at a time
 // A step of the walk takes up to kBatchGroups sibling groups off the stack and
 // stages all their children at once, 8 lanes per group.
-constexpr int kBatchGroups = 6;
+constexpr int kBatchGroups = 6;  // storing walk
 constexpr int kBatchGroupsF64 = 4;  // the FP64 walk's 64-byte staged records (7 waves per SIMD)
 // Stack bound.  Taking one group and pushing the groups of its opened
 // children (at most 8) grows the stack by at most 7 per level below the
@@ -53,12 +33,7 @@ constexpr int kBatchGroupsF64 = 4;  // the FP64 walk's 64-byte staged records (7
 // kStackBatch + 141 <= kStack.  A push beyond the stack therefore cannot
 // happen; it would be refused and flagged (status bit 0).
 constexpr int kStackDfs = 7 * 20 + 1;
-// 248 entries: the F32C walk's 4-wave block (stack, 48 staged children) takes
-// 20 192 bytes and fits 8 to a CU's LDS (allocated in 512-byte granules).
 constexpr int kStackMulti = 248;
-// The FP64 walk's 64-byte staged records leave less room: with 256 entries its
-// 4-wave block (22 272 bytes) fits 7 to a CU, with 272 only 6.
-constexpr int kStackMultiF64 = 256;
 // The adjoint walk keeps its gradients in LDS as well; it takes one group per
 // step and a depth-first stack (<= 141 groups), which keeps 7 waves per SIMD.
 constexpr int kStackSingle = 160;
@@ -89,30 +64,22 @@ struct __align__(16) Hot64 {
     uint32_t first, count, child, pad;
 };
 
-// ADJ = false: accelerations and potentials; with STORE it also records, per
-// wave and in visit order, every (node, accepting lanes) pair and every
-// multi-particle leaf opened with its lanes.  ADJ = true: the adjoint walk
-// with identical decisions and arithmetic, which writes the target-side
-// gradient per particle and accumulates the source-side gradients per node
-// (and per particle for opened multi-particle leaves) with FP64 atomics after
-// a wave reduction.  It replays the wave's stored records when there are
-// valid ones and re-walks the tree otherwise.
-// The walk is bound by latency at full occupancy, so the timed forward walks
-// are held to 64 VGPRs (8 waves per SIMD); both need the request.
-template <bool F64, bool COUNT, bool ADJ, bool STORE>
-__global__ __launch_bounds__(kWalkThreads) __attribute__((amdgpu_waves_per_eu((!COUNT && !ADJ && !STORE) ? 8 : 1)))
-void k_walk(WalkArgs a)
+// ADJ = false: the storing walk (accelerations and potentials, and the records).
+// ADJ = true: the adjoint walk, which writes the target-side gradient per
+// particle and accumulates the source-side gradients per node (and per particle
+// for opened multi-particle leaves) with FP64 atomics after a wave reduction.
+// It replays the wave's stored records when there are valid ones and re-walks
+// the tree otherwise.
+template <bool F64, bool COUNT, bool ADJ>
+__global__ __launch_bounds__(kWalkThreads) void k_walk(WalkArgs a)
 {
-    static_assert(!(ADJ && (COUNT || STORE)), "the adjoint walk neither counts nor stores");
-    // the straight run over decided accepts: the forward walks (the adjoint and
-    // the storing walk act per node with wave-wide steps, and take every child
-    // through the general path)
-    constexpr bool FAST = !ADJ && !STORE;
+    static_assert(!(ADJ && COUNT), "the adjoint walk does not count");
+    constexpr bool STORE = !ADJ;
     using R = typename std::conditional<F64, double, float>::type;
     using Hot = typename std::conditional<F64, Hot64, Hot32>::type;
     // groups per step and the stack they need
     constexpr int kGroups = ADJ ? 1 : (F64 ? kBatchGroupsF64 : kBatchGroups);
-    constexpr int kStack = kGroups == 1 ? kStackSingle : (F64 ? kStackMultiF64 : kStackMulti);
+    constexpr int kStack = kGroups == 1 ? kStackSingle : kStackMulti;
     constexpr int kStackBatch = kStack - kStackDfs - 7;
     // the stack of pending sibling groups: first node, child count, lanes that opened the parent
     // (several groups per step: three arrays, 13 bytes an entry, so that the deeper stack
@@ -507,62 +474,17 @@ void k_walk(WalkArgs a)
                 vis_ovl += __popc((uint32_t)(ovl_m >> (8 * j)) & ((1u << nc) - 1u));
             }
             const uint32_t all = (1u << nc) - 1u;
-            // decided accepted by every target, and not holding any (the forward
-            // walks take these in one straight run with the active lanes enabled;
-            // the others take them through the general path without the tests)
+            // decided accepted by every target, and not holding any: no tests needed
             const uint32_t far_bits = (uint32_t)(far_all >> (8 * j)) & all;
-            uint32_t fast = FAST ? far_bits : 0u;
             // decided opened by every active target
-            uint32_t opened = (uint32_t)(near_all >> (8 * j)) & all & ~fast;
-            const uint32_t slow = all & ~fast & ~opened;
+            uint32_t opened = (uint32_t)(near_all >> (8 * j)) & all & ~far_bits;
+            const uint32_t slow = all & ~opened;
             if constexpr (COUNT) {
-                vis_allacc += __popc(fast);
-                vis_boxacc += __popc(fast);
+                vis_boxacc += __popc(far_bits);
                 vis_noacc += __popc(opened);
                 vis_boxopen += __popc(opened);
             }
             const Hot* g8 = &stg[w][8 * j];
-            if (fast && __builtin_amdgcn_inverse_ballot_w64(mask)) {
-                // no opening test here, so the softening enters the distance chain
-                if constexpr (!F64) {
-                    // each slot's position and mass are read while the slot before it is
-                    // evaluated, so the LDS latency is not paid child by child (the FP64
-                    // walk's 32-byte reads gain nothing from it)
-                    float4 hc = *reinterpret_cast<const float4*>(&g8[0]);
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const float4 hn = k < 7 ? *reinterpret_cast<const float4*>(&g8[k + 1]) : hc;
-                        if ((fast >> k) & 1u) {
-                            const R dx = hc.x - px, dy = hc.y - py, dz = hc.z - pz;
-                            const R ri = rsqrt_any(fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2))));
-                            const R mr = hc.w * ri;
-                            const R mr3 = mr * (ri * ri);
-                            bx = fma(mr3, dx, bx);
-                            by = fma(mr3, dy, by);
-                            bz = fma(mr3, dz, bz);
-                            bp -= mr;
-                            if constexpr (COUNT) ++nint;
-                        }
-                        hc = hn;
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        if ((fast >> k) & 1u) {
-                            const Hot h = g8[k];
-                            const R dx = h.x - px, dy = h.y - py, dz = h.z - pz;
-                            const R ri = rsqrt_any(fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2))));
-                            const R mr = h.m * ri;
-                            const R mr3 = mr * (ri * ri);
-                            bx = fma(mr3, dx, bx);
-                            by = fma(mr3, dy, by);
-                            bz = fma(mr3, dz, bz);
-                            bp -= mr;
-                            if constexpr (COUNT) ++nint;
-                        }
-                    }
-                }
-            }
             // an opened child: its own group is pushed, or an opened leaf's particles
             // are taken one by one, the target itself excluded (for a one-particle
             // leaf only the lane holding that particle gets here, and it contributes nothing)
@@ -608,7 +530,7 @@ void k_walk(WalkArgs a)
                 const R d2 = fma(dx, dx, fma(dy, dy, dz * dz));
                 // lane masks combined on the scalar unit: accepted = active, not containing, far enough
                 uint64_t am = mask;
-                if (FAST || !((far_bits >> k) & 1u)) {
+                if (!((far_bits >> k) & 1u)) {
                     uint64_t in_m = 0;
                     if ((ovl_m >> slot) & 1ull) in_m = __ballot((su - h.first) < h.count);
                     am &= __ballot(d2 > h.tau) & ~in_m;
@@ -740,25 +662,18 @@ void k_walk(WalkArgs a)
 
 int64_t walk_waves(int64_t n) { return (n + 63) / 64; }
 
-template <bool F64>
-void launch_walk_t(const WalkArgs& a, unsigned blocks, bool count, bool store, hipStream_t s)
-{
-    if (count) {
-        if (store) k_walk<F64, true, false, true><<<blocks, kWalkThreads, 0, s>>>(a);
-        else k_walk<F64, true, false, false><<<blocks, kWalkThreads, 0, s>>>(a);
-    } else {
-        if (store) k_walk<F64, false, false, true><<<blocks, kWalkThreads, 0, s>>>(a);
-        else k_walk<F64, false, false, false><<<blocks, kWalkThreads, 0, s>>>(a);
-    }
-}
-
-void launch_walk(const WalkArgs& a, tc_walk mode, bool count, bool store, hipStream_t s)
+void launch_walk(const WalkArgs& a, tc_walk mode, bool count, hipStream_t s)
 {
     if (a.n == 0) return;
     const int64_t waves = walk_waves(a.n);
     const unsigned blocks = (unsigned)((waves + kWalkWaves - 1) / kWalkWaves);
-    if (mode == TC_WALK_F64) launch_walk_t<true>(a, blocks, count, store, s);
-    else launch_walk_t<false>(a, blocks, count, store, s);
+    if (mode == TC_WALK_F64) {
+        if (count) k_walk<true, true, false><<<blocks, kWalkThreads, 0, s>>>(a);
+        else k_walk<true, false, false><<<blocks, kWalkThreads, 0, s>>>(a);
+    } else {
+        if (count) k_walk<false, true, false><<<blocks, kWalkThreads, 0, s>>>(a);
+        else k_walk<false, false, false><<<blocks, kWalkThreads, 0, s>>>(a);
+    }
 }
 
 void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s)
@@ -766,8 +681,8 @@ void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s)
     if (a.n == 0) return;
     const int64_t waves = walk_waves(a.n);
     const unsigned blocks = (unsigned)((waves + kWalkWaves - 1) / kWalkWaves);
-    if (mode == TC_WALK_F64) k_walk<true, false, true, false><<<blocks, kWalkThreads, 0, s>>>(a);
-    else k_walk<false, false, true, false><<<blocks, kWalkThreads, 0, s>>>(a);
+    if (mode == TC_WALK_F64) k_walk<true, false, true><<<blocks, kWalkThreads, 0, s>>>(a);
+    else k_walk<false, false, true><<<blocks, kWalkThreads, 0, s>>>(a);
 }
 
 }  // namespace tc

@@ -89,14 +89,15 @@ __device__ inline void wave_sum4(R& a0, R& a1, R& a2, R& a3)
 }
 
 // Sum over each 16-lane row of the wave (DPP: xor 1, xor 2, half-row
-// mirror, row mirror); afterwards every lane holds its row's sum.
+// mirror, row mirror; every lane active, so that bound_ctrl changes nothing but
+// lets the move fold into the addition); afterwards every lane holds its row's sum.
 __device__ inline float dpp_f(float v, int ctrl)
 {
     switch (ctrl) {  // the control word must be a constant
-    case 0: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
-    case 1: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));
-    case 2: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, false));
-    default: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, false));
+    case 0: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));
+    case 1: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));
+    case 2: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true));
+    default: return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x140, 0xF, 0xF, true));
     }
 }
 
@@ -105,10 +106,10 @@ __device__ inline double dpp_d(double v, int ctrl)
     const long long b = __double_as_longlong(v);
     int lo = (int)(b & 0xFFFFFFFF), hi = (int)(b >> 32);
     switch (ctrl) {
-    case 0: lo = __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xF, 0xF, false); hi = __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xF, 0xF, false); break;
-    case 1: lo = __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xF, 0xF, false); hi = __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xF, 0xF, false); break;
-    case 2: lo = __builtin_amdgcn_mov_dpp(lo, 0x141, 0xF, 0xF, false); hi = __builtin_amdgcn_mov_dpp(hi, 0x141, 0xF, 0xF, false); break;
-    default: lo = __builtin_amdgcn_mov_dpp(lo, 0x140, 0xF, 0xF, false); hi = __builtin_amdgcn_mov_dpp(hi, 0x140, 0xF, 0xF, false); break;
+    case 0: lo = __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xF, 0xF, true); hi = __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xF, 0xF, true); break;
+    case 1: lo = __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xF, 0xF, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xF, 0xF, true); break;
+    case 2: lo = __builtin_amdgcn_mov_dpp(lo, 0x141, 0xF, 0xF, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x141, 0xF, 0xF, true); break;
+    default: lo = __builtin_amdgcn_mov_dpp(lo, 0x140, 0xF, 0xF, true); hi = __builtin_amdgcn_mov_dpp(hi, 0x140, 0xF, 0xF, true); break;
     }
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
@@ -142,6 +143,32 @@ __device__ inline R slot_sum(R v)
         else v += dpp_f(v, c);
     }
     return v;
+}
+
+// Lane `at` (uniform) of (lo, hi) takes the uniform value v.
+__device__ inline void write_lane(uint32_t& lo, uint32_t& hi, uint64_t v, uint32_t at)
+{
+    asm volatile("s_mov_b32 m0, %4\n\t"
+                 "s_nop 1\n\t"
+                 "v_writelane_b32 %0, %2, m0\n\t"
+                 "v_writelane_b32 %1, %3, m0"
+                 : "+v"(lo), "+v"(hi)
+                 : "s"((uint32_t)v), "s"((uint32_t)(v >> 32)), "s"(at)
+                 : "m0");
+}
+
+// The value that lane `from` (taken modulo 64) holds.
+__device__ inline float lane_pull(float v, uint32_t from)
+{
+    return __int_as_float(__builtin_amdgcn_ds_bpermute((int)(from << 2), __float_as_int(v)));
+}
+
+__device__ inline double lane_pull(double v, uint32_t from)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_ds_bpermute((int)(from << 2), (int)(b & 0xFFFFFFFF));
+    const int hi = __builtin_amdgcn_ds_bpermute((int)(from << 2), (int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
 // Count of set bits of m strictly below this lane.

@@ -1,6 +1,6 @@
 // The walk for few particles: a wavefront serves T = 8 or 16 targets.
 //
-// A wavefront that serves 64 targets (walk.hip) evaluates one node at a time for
+// A wavefront that serves 64 targets (walk_forward.hip) evaluates one node at a time for
 // all of them.  Below ~1e5 particles there are fewer such wavefronts than the
 // chip has places for, and each is a long serial chain: a lone wavefront issues
 // an instruction every ~8 cycles, whatever its dependences.  Here lane
@@ -8,17 +8,17 @@
 // evaluated at once, there are 64 / T times more wavefronts, and each has a
 // correspondingly shorter chain (the T targets lie closer together, so they also
 // open fewer nodes between them).  The price is that a node record is staged for
-// T targets instead of 64, which is why large inputs stay with walk.hip.
+// T targets instead of 64, which is why large inputs stay with walk_forward.hip.
 //
 // A step takes up to 8 sibling groups off the stack and stages their <= 64
-// children, one per lane.  The box test of walk.hip sorts the children into
+// children, one per lane.  The box test of walk_forward.hip sorts the children into
 // accepted by every target (list A, compacted in LDS), opened by every target of
 // the group's mask, and undecided (list M).  The slots take the entries of A in
 // one straight run; those of M with the per-target rule, which leaves each
 // entry's mask of opening targets in LDS.  Then all opened children push their
 // groups at once, each at the place that a prefix count gives it.
 //
-// Decisions are those of walk.hip, bit for bit: the FP32 offsets come from the
+// Decisions are those of walk_forward.hip, bit for bit: the FP32 offsets come from the
 // same anchor (the first target of the aligned 64), through the same operations.
 // Only the order of the sums differs; the slots' partial sums are added in FP64.
 #include <type_traits>
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
             if (a.g_pot) hl = Gc * ((const R*)a.g_pot)[i];
         }
     }
-    // the sorted range the targets span and their bounding box (see walk.hip)
+    // the sorted range the targets span and their bounding box (see walk_forward.hip)
     uint32_t smin = su, smax = su;
     R bnx = px, bny = py, bnz = pz, bxx = px, bxy = py, bxz = pz;
 #pragma unroll
@@ -191,7 +191,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
             const R tau = meta_single(meta) ? (R)-1 : (R)ldexp(tau0, -2 * (int)meta_level(meta));
             stau[w][lane] = tau;
             srange[w][lane] = make_uint2(first, count);
-            // the box test of walk.hip: decided for every target of the wavefront
+            // the box test of walk_forward.hip: decided for every target of the wavefront
             const R gx = fmax(fmax(bnx - h.x, h.x - bxx), (R)0), fx = fmax(fabs(h.x - bnx), fabs(h.x - bxx));
             const R gy = fmax(fmax(bny - h.y, h.y - bxy), (R)0), fy = fmax(fabs(h.y - bny), fabs(h.y - bxy));
             const R gz = fmax(fmax(bnz - h.z, h.z - bxz), (R)0), fz = fmax(fabs(h.z - bnz), fabs(h.z - bxz));
@@ -228,7 +228,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
                 mc = mn;
             }
         }
-        // list M: the per-target rule (walk.hip: accepted = active, not containing, far enough)
+        // list M: the per-target rule (accepted = active, not containing, far enough)
         for (int e0 = na_pad; e0 < end; e0 += S) {
             const Rec hc = rec[w][e0 + (int)s];
             const uint32_t mc = rmask[w][e0 + (int)s];
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
             const uint32_t om = (uint32_t)__builtin_amdgcn_readlane((int)open, src);
             const bool lane_open = (om & tbit) != 0u;
             for (uint32_t j0 = 0; j0 < cnt; j0 += S) {
-                // separations in FP64: the particles share a level-21 cell (see walk.hip)
+                // separations in FP64: the particles share a level-21 cell (see walk_forward.hip)
                 const uint32_t j = f + j0 + s;
                 const bool in = j0 + s < cnt;
                 const Particle pj = a.sp[in ? j : f];
@@ -372,18 +372,18 @@ void launch_split(const WalkArgs& a, tc_walk mode, hipStream_t s)
 
 }  // namespace
 
-// Where the lines lie (walk times in us on one MI355X, theta = 0.6 up to 2^18 and
-// 0.5 above, T = 8 / 16 / 64):
-//   F32C  16384: 54 / 78 / 328    65536: 118 / 108 / 365    262144: 408 / 324 / 449
-//         524288: 1247 / 933 / 989    1000000: 2334 / 1717 / 1663
-//   FP64  16384: 62 / 83 / 404    65536: 162 / 153 / 459    262144: 581 / 485 / 705
-//         1000000: 3360 / 2764 / 2953    4000000: 13900 / 11281 / 10704
+// Where the lines lie (walk times in us on one MI355X, Plummer, theta = 0.5,
+// T = 8 / 16 / 64):
+//   F32C  32768: 95 / 118 / 413     49152: 143 / 135 / 439    131072: 300 / 262 / 482
+//         262144: 575 / 469 / 548   524288: 1136 / 898 / 813
+//   FP64  65536: 225 / 216 / 510    262144: 845 / 718 / 839
+//         524288: 1694 / 1415 / 1450    1000000: 3273 / 2704 / 2375
 // The FP64 term costs about twice the FP32 one and the staging the same, so the
 // better-filled lanes of 16 targets pay for longer there.
 int walk_targets(int64_t n, tc_walk mode)
 {
-    if (n <= 49152) return 8;
-    return n <= (mode == TC_WALK_F64 ? 1 << 21 : 1 << 19) ? 16 : 64;
+    if (n <= 5 << 13) return 8;
+    return n <= (mode == TC_WALK_F64 ? 1 << 19 : 3 << 17) ? 16 : 64;
 }
 
 // The adjoint adds to a node's gradient with four atomics per wavefront and node,

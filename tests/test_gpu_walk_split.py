@@ -64,8 +64,8 @@ def test_split_walks_match_oracle(name, make, theta, eps, walk):
     assert abs(st["sum_m_abs_a"] / (md * np.linalg.norm(ra, axis=1)).sum() - 1) < 1e-6
 
 
-@pytest.mark.parametrize("walk,n", [("f32c", 49152), ("f32c", 49153), ("f32c", 524288), ("f32c", 524289),
-                                    ("f64", 49153), ("f64", 2097152), ("f64", 2097153)])
+@pytest.mark.parametrize("walk,n", [("f32c", 40960), ("f32c", 40961), ("f32c", 393216), ("f32c", 393217),
+                                    ("f64", 40961), ("f64", 524288), ("f64", 524289)])
 def test_both_sides_of_the_lines(walk, n):
     import paper_2412_01733_amd as tc
     print("case", walk, n, flush=True)
@@ -76,3 +76,37 @@ def test_both_sides_of_the_lines(walk, n):
     acc, pot = tree.forces(0.7, 0.01, walk=walk)
     check_errors(rel_err(acc.cpu().numpy(), a64.cpu().numpy()), walk, what="acc")
     check_errors(rel_err(pot.cpu().numpy(), p64.cpu().numpy()), walk, what="pot")
+
+
+@pytest.mark.parametrize("walk", ["f32c", "f64"])
+@pytest.mark.parametrize("name", ["plummer", "clumps", "dups", "wide_theta"])
+def test_wide_walk_matches_oracle(name, walk):
+    """The 64-target walk as large inputs take it (above the lines it is the same
+    kernel that counts, so a counting call stands for it here), with masks of
+    every density: compact clumps seen from afar, outliers whose wavefronts are
+    spread out, leaves of several particles, theta > 1/sqrt(3)."""
+    import paper_2412_01733_amd as tc
+    print("case", name, walk, flush=True)
+    theta, eps = 0.5, 0.005
+    if name == "plummer":
+        pos, m = workloads.plummer(30011, 3)
+    elif name == "clumps":
+        ctr = np.array([[x, y, z] for x in (0, 3) for y in (0, 5) for z in (0, 9)], float)
+        pos, m = workloads.clumps(1501, ctr, 0.02, 5)
+        pos[::50] += np.random.default_rng(1).normal(0, 4.0, pos[::50].shape)
+    elif name == "dups":
+        pos, m = _dups(9001, 8)
+        eps = 0.001
+    else:
+        pos, m = workloads.plummer(12001, 4)
+        theta = 1.3
+    p, mm = _gpu(pos, m)
+    acc, pot, tree = tc.forces(p, mm, theta, eps, walk=walk, count=True)
+    T = oracle.Tree(pos, m)
+    ra, rp, nint = T.forces(theta, eps)
+    counts = tree.interaction_counts().cpu().numpy().astype(np.int64)
+    assert np.mean(counts != nint) < (0.01 if walk == "f32c" else 1e-3)
+    check_errors(rel_err(acc.cpu().numpy(), ra), walk, counts == nint, "acc")
+    check_errors(rel_err(pot.cpu().numpy(), rp), walk, counts == nint, "pot")
+    again, _, _ = tc.forces(p, mm, theta, eps, walk=walk, count=True)
+    assert torch.equal(acc, again)
