@@ -453,7 +453,7 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
     stage_begin(t, kStWalk, s);
     if (targets < 64) launch_walk_split(a, targets, mode, s);
     else if (store) launch_walk(a, mode, t->counted, s);
-    else launch_walk_forward(a, mode, t->counted, s);
+    else launch_walk_forward(a, mode, t->counted, walk_team(n, mode), s);
     stage_end(t, kStWalk, s);
     TC_TRY(check_launch("walk"));
     stage_begin(t, kStDiag, s);
@@ -499,8 +499,9 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     launch_fill_f64_zero(a.node_grad, nn * 4, s);
     launch_fill_f64_zero(a.part_grad, n * 4, s);
     const int targets = t->lists_stored ? 64 : adjoint_targets(n, t->last_mode);
-    if (targets < 64) launch_walk_split_adjoint(a, targets, t->last_mode, s);
-    else launch_walk_adjoint(a, t->last_mode, s);
+    if (targets < 64) launch_walk_split_adjoint(a, t->last_mode, s);
+    else if (t->lists_stored) launch_walk_adjoint(a, t->last_mode, s);
+    else launch_walk_adjoint_wide(a, t->last_mode, adjoint_team(n, t->last_mode), s);
     stage_end(t, kStBwdWalk, s);
     TC_TRY(check_launch("adjoint walk"));
     HIP_TRY(hipMemcpyAsync(&t->host->status, t->status, 4, hipMemcpyDeviceToHost, s));

@@ -160,15 +160,20 @@ int64_t walk_waves(int64_t n);
 // storing walk (with or without counting)
 void launch_walk(const WalkArgs& a, tc_walk mode, bool count, hipStream_t s);
 // walk_forward.hip: the walk that does not store
-void launch_walk_forward(const WalkArgs& a, tc_walk mode, bool count, hipStream_t s);
+void launch_walk_forward(const WalkArgs& a, tc_walk mode, bool count, bool team, hipStream_t s);
+// adjoint walk: replays stored lists, or walks for the wavefronts that have none
 void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
+// walk_adjoint.hip: the adjoint walk where no lists are stored
+void launch_walk_adjoint_wide(const WalkArgs& a, tc_walk mode, bool team, hipStream_t s);
 
-// walk_split.hip: the same walks with `targets` (8 or 16) targets a wavefront;
-// walk_targets / adjoint_targets: which to use for n particles (64: walk_forward.hip, walk.hip)
+// walk_split.hip: the same walks with 8 or 16 targets a wavefront (the adjoint: 8).
+// Targets a wavefront for n particles, and, of 64, whether a team of wavefronts takes them.
 int walk_targets(int64_t n, tc_walk mode);
+bool walk_team(int64_t n, tc_walk mode);
 int adjoint_targets(int64_t n, tc_walk mode);
+bool adjoint_team(int64_t n, tc_walk mode);
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
-void launch_walk_split_adjoint(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
+void launch_walk_split_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 
 // order.hip: the walk's target order (Hilbert order of the particles); also
 // up[node] = {distance of the node from its parent's start in the order, parent}.

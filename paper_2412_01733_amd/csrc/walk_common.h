@@ -13,6 +13,14 @@ __device__ inline void wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// What separates a step's LDS accesses: TEAM wavefronts of a block share the stack, or one has its own.
+template <int TEAM>
+__device__ inline void team_sync()
+{
+    if constexpr (TEAM > 1) __syncthreads();
+    else wave_sync();
+}
+
 __device__ inline uint32_t uni(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ inline float uni_r(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
@@ -65,14 +73,14 @@ __device__ inline void adj_term(R dx, R dy, R dz, R q, R mu, R gx, R gy, R gz, R
 {
     const R ri = rsqrt_any(q);
     const R ri2 = ri * ri;
-    const R ri3 = ri2 * ri;
     const R dg = fma(dx, gx, fma(dy, gy, dz * gz));
-    const R c1 = mu * ri3;
-    const R c2 = c1 * fma((R)-3 * ri2, dg, h);
+    const R e = dg * ri2, w = h - e;
+    const R c1 = mu * ri * ri2;
+    const R c2 = c1 * fma((R)-2, e, w);  // mu q^-3/2 (h - 3 Delta.g / q)
     sx = fma(c1, gx, c2 * dx);
     sy = fma(c1, gy, c2 * dy);
     sz = fma(c1, gz, c2 * dz);
-    sm = fma(dg, ri3, -h * ri);
+    sm = -ri * w;
 }
 
 // Sum over the wave of four values; the result is uniform.
@@ -145,22 +153,44 @@ __device__ inline R slot_sum(R v)
     return v;
 }
 
-// Lane `at` (uniform) of (lo, hi) takes the uniform value v.
-__device__ inline void write_lane(uint32_t& lo, uint32_t& hi, uint64_t v, uint32_t at)
+// Exchanges lanes 32-63 of a with lanes 0-31 of b.
+__device__ inline void half_swap(float& a, float& b)
 {
-    asm volatile("s_mov_b32 m0, %4\n\t"
-                 "s_nop 1\n\t"
-                 "v_writelane_b32 %0, %2, m0\n\t"
-                 "v_writelane_b32 %1, %3, m0"
-                 : "+v"(lo), "+v"(hi)
-                 : "s"((uint32_t)v), "s"((uint32_t)(v >> 32)), "s"(at)
-                 : "m0");
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)__float_as_int(a), (unsigned)__float_as_int(b), false, false);
+    a = __int_as_float((int)r[0]);
+    b = __int_as_float((int)r[1]);
+}
+
+__device__ inline void half_swap(double& a, double& b)
+{
+    const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(x >> 32), (unsigned)(y >> 32), false, false);
+    a = __longlong_as_double((long long)(((uint64_t)hi[0] << 32) | lo[0]));
+    b = __longlong_as_double((long long)(((uint64_t)hi[1] << 32) | lo[1]));
+}
+
+// Sum over aligned runs of N = 2, 4 or 8 lanes.
+template <uint32_t N, typename R>
+__device__ inline R part_sum(R v)
+{
+#pragma unroll
+    for (int c = 0; c < (N == 8 ? 3 : N == 4 ? 2 : 1); ++c) {
+        if constexpr (sizeof(R) == 8) v += dpp_d(v, c);
+        else v += dpp_f(v, c);
+    }
+    return v;
 }
 
 // The value that lane `from` (taken modulo 64) holds.
 __device__ inline float lane_pull(float v, uint32_t from)
 {
     return __int_as_float(__builtin_amdgcn_ds_bpermute((int)(from << 2), __float_as_int(v)));
+}
+
+__device__ inline uint32_t lane_pull_u(uint32_t v, uint32_t from)
+{
+    return (uint32_t)__builtin_amdgcn_ds_bpermute((int)(from << 2), (int)v);
 }
 
 __device__ inline double lane_pull(double v, uint32_t from)

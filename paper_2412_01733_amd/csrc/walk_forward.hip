@@ -70,6 +70,12 @@ constexpr uint32_t kXcdRun = 64;  // consecutive blocks one XCD takes at a time
 //   registers spilled) 12.12; never transposed 12.67; groups of up to 16 lanes
 //   transposed as well (4 children x 16 targets, twice) 12.83.
 //   FP64 (ms): 6 groups 22.55, 7 groups 22.26, 8 groups 21.97; never transposed 25.4.
+// A team: the four wavefronts of a block serve the same 64 targets, share one
+// stack and take a quarter of each step's groups each, so that a walk is a
+// quarter as long: with fewer than ~10 wavefronts per place on the chip the
+// tail and the lone chains cost more than the two barriers of a step.
+constexpr int kTeamStack = 400;
+
 template <bool F64> struct FwdShape {
     static constexpr int groups = F64 ? 8 : 6;
     static constexpr int stack = F64 ? 180 : 190;
@@ -78,22 +84,27 @@ template <bool F64> struct FwdShape {
     static_assert(stack >= 142, "the root's children must be safe");
 };
 
-template <bool F64, bool COUNT>
+template <bool F64, bool COUNT, int TEAM>
 __global__ __launch_bounds__(kFwdThreads) __attribute__((amdgpu_waves_per_eu(COUNT ? 1 : FwdShape<F64>::waves)))
 void k_walk_fwd(WalkArgs a)
 {
     using R = typename std::conditional<F64, double, float>::type;
     using Shape = FwdShape<F64>;
-    constexpr int kGroups = Shape::groups, kStack = Shape::stack, kSlots = 64;
+    constexpr int kGroups = Shape::groups, kStack = TEAM > 1 ? kTeamStack : Shape::stack, kSlots = 64;
+    constexpr int kStacks = TEAM > 1 ? 1 : kFwdWaves;
+    static_assert(TEAM == 1 || TEAM == kFwdWaves, "a team is a block");
     struct __align__(16) Pos { R x, y, z, m; };
     struct __align__(16) Aux { R tau; uint32_t first, count; };  // opening threshold (-1: a one-particle leaf), particle range
     struct __align__(16) Tgt { R x, y, z; };
-    __shared__ uint64_t stk_m[kFwdWaves][kStack];  // lanes that opened the parent
-    __shared__ uint32_t stk_gs[kFwdWaves][kStack]; // first node
-    __shared__ uint8_t stk_b[kFwdWaves][kStack];   // child count - 1 | level of the nodes << 3
-    __shared__ Pos spos[kFwdWaves][kSlots];        // staged children: slot 8 j + k holds child k of group j
-    __shared__ Aux saux[kFwdWaves][kSlots];
+    __shared__ uint64_t stk_m[kStacks][kStack];  // lanes that opened the parent
+    __shared__ uint32_t stk_gs[kStacks][kStack]; // first node
+    __shared__ uint8_t stk_b[kStacks][kStack];   // child count - 1 | level of the nodes << 3
+    // staged children: slot 8 j + k holds child k of group j; after the walk a team's totals
+    constexpr int kTotals = 4;
+    struct __align__(16) Stage { Pos pos[kSlots]; Aux aux[kSlots]; };
+    __shared__ union { Stage st[kFwdWaves]; double total[TEAM][kTotals][64]; } stage;
     __shared__ Tgt tgt[kFwdWaves][8];          // a sparse group's targets
+    __shared__ uint32_t pushes[2][TEAM];
     R tau0;
     if constexpr (F64) tau0 = a.tau0_64;
     else tau0 = a.tau0_32;
@@ -101,6 +112,7 @@ void k_walk_fwd(WalkArgs a)
     // FP64: the wave index made uniform keeps the per-wave LDS slices in scalar registers
     const int w = F64 ? uni((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
+    const int sw = TEAM > 1 ? 0 : w;  // whose stack
     // Workgroups are dealt to the 8 XCDs round-robin.  Dealing runs of
     // kXcdRun consecutive blocks instead (a bijection on whole rounds of 8
     // runs, the identity on the tail) keeps each XCD's L2 on compact regions
@@ -108,9 +120,9 @@ void k_walk_fwd(WalkArgs a)
     const uint32_t nb = gridDim.x, b = blockIdx.x, full = nb / (8 * kXcdRun) * (8 * kXcdRun);
     const uint32_t i8 = b >> 3;
     const uint32_t lb = b < full ? ((i8 / kXcdRun) * 8 + (b & 7u)) * kXcdRun + i8 % kXcdRun : b;
-    const int64_t wave_id = (int64_t)lb * kFwdWaves + w;
+    const int64_t wave_id = TEAM > 1 ? (int64_t)lb : (int64_t)lb * kFwdWaves + w;  // 64 targets
     const int64_t base = wave_id * 64;
-    if (base >= a.n) return;  // whole wave; no block barrier follows
+    if (base >= a.n) return;  // the whole wave; of a team, the whole block
     // this lane's target (sorted position) and the range of sorted positions the
     // wavefront's targets span (a superset of them: only a node overlapping it
     // can hold one of the targets)
@@ -161,36 +173,51 @@ void k_walk_fwd(WalkArgs a)
     const uint32_t rmeta = uni(a.nodes[0].meta);
     if (!meta_leaf(rmeta)) {
         const uint64_t vmask = __ballot(valid);
-        if (lane == 0) {
-            stk_m[w][0] = vmask;
-            stk_gs[w][0] = uni(a.nodes[0].child);
-            stk_b[w][0] = (uint8_t)((meta_nchild(rmeta) - 1u) | (1u << 3));
+        if (lane == 0 && w == sw) {
+            stk_m[sw][0] = vmask;
+            stk_gs[sw][0] = uni(a.nodes[0].child);
+            stk_b[sw][0] = (uint8_t)((meta_nchild(rmeta) - 1u) | (1u << 3));
         }
         sp = 1;
     }
-    wave_sync();
+    team_sync<TEAM>();
 
     const uint32_t gj = lane >> 3, gk = lane & 7;
     bool stack_over = false;
     uint32_t most = 0;  // children of a staged node at most (more than 8: a corrupt tree)
-    int since_fold = 0;
+    int since_fold = 0, turn = 0;
     while (sp > 0) {
         // take the groups that the stack bound allows off the top; lanes 8 j .. 8 j + 7 stage
         // group j.  Idle lanes do the same work on the bottom entry and node 0, and are
         // masked out of the ballots: no divergence, so the ballots read the compares.
-        const int at = max(sp - 1 - (int)gj, 0);
-        const uint32_t gs = stk_gs[w][at], gb = stk_b[w][at];
+        int ng, q, j0;  // groups the step takes, of them at most q by this wave, from the j0-th off the top
+        if constexpr (TEAM == 1) {
+            q = kGroups;
+            j0 = 0;
+        } else {
+            const uint32_t lb_ = stk_b[0][max(sp - 1 - (int)lane, 0)];
+            const uint64_t okm = __ballot((int)lane < min(sp, TEAM * kGroups)) &
+                                 __ballot(sp + 7 * ((int)lane + 1) + 7 * (20 - (int)(lb_ >> 3)) + 1 <= kStack);
+            ng = uni(~okm ? (int)__builtin_ctzll(~okm) : 64);
+            q = (ng + TEAM - 1) / TEAM;
+            j0 = uni(w * q);
+        }
+        const int at = max(sp - 1 - j0 - (int)gj, 0);
+        const uint32_t gs = stk_gs[sw][at], gb = stk_b[sw][at];
         uint32_t om_lo, om_hi;  // the group's mask, later the child's opening lanes
         {
-            const uint64_t m = stk_m[w][at];
+            const uint64_t m = stk_m[sw][at];
             om_lo = (uint32_t)m;
             om_hi = (uint32_t)(m >> 32);
         }
-        const uint64_t okm = __ballot((int)gj < min(sp, kGroups)) &
-                             __ballot(sp + 7 * ((int)gj + 1) + 7 * (20 - (int)(gb >> 3)) + 1 <= kStack);
-        const int ng = uni(~okm ? (int)(__builtin_ctzll(~okm) >> 3) : 8);
+        if constexpr (TEAM == 1) {
+            const uint64_t okm = __ballot((int)gj < min(sp, kGroups)) &
+                                 __ballot(sp + 7 * ((int)gj + 1) + 7 * (20 - (int)(gb >> 3)) + 1 <= kStack);
+            ng = uni(~okm ? (int)(__builtin_ctzll(~okm) >> 3) : 8);
+        }
+        const int mine = TEAM == 1 ? ng : max(0, min(q, ng - j0));
         sp = uni(sp - ng);
-        const bool live = (int)gj < ng && gk <= (gb & 7u);
+        const bool live = (int)gj < mine && gk <= (gb & 7u);
         const uint64_t live_m = __ballot(live);
         const WalkNode nd = a.nodes[live ? gs + gk : 0u];
         Pos h;
@@ -205,8 +232,8 @@ void k_walk_fwd(WalkArgs a)
         // opening threshold tau0 4^-l (an exact power-of-two scaling); a
         // one-particle leaf is always taken (-1)
         const R tau = meta_single(meta) ? (R)-1 : (R)ldexp(tau0, -2 * (int)meta_level(meta));
-        spos[w][lane] = h;
-        saux[w][lane] = Aux{tau, nd.first, nd.count};
+        stage.st[w].pos[lane] = h;
+        stage.st[w].aux[lane] = Aux{tau, nd.first, nd.count};
         const R gx = fmax(fmax(bnx - h.x, h.x - bxx), (R)0), fx = fmax(fabs(h.x - bnx), fabs(h.x - bxx));
         const R gy = fmax(fmax(bny - h.y, h.y - bxy), (R)0), fy = fmax(fabs(h.y - bny), fabs(h.y - bxy));
         const R gz = fmax(fmax(bnz - h.z, h.z - bxz), (R)0), fz = fmax(fabs(h.z - bnz), fabs(h.z - bxz));
@@ -227,13 +254,13 @@ void k_walk_fwd(WalkArgs a)
         }
         wave_sync();
 
-        for (int j = 0; j < ng; ++j) {
+        for (int j = 0; j < mine; ++j) {
             const uint64_t mask = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)om_lo, 8 * j) |
                                   ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)om_hi, 8 * j) << 32);
             uint32_t fast = (uint32_t)(far_m >> (8 * j)) & 0xFFu;
             uint32_t mixed = (uint32_t)(mixed_m >> (8 * j)) & 0xFFu;
-            const Pos* g8 = &spos[w][8 * j];
-            const Aux* x8 = &saux[w][8 * j];
+            const Pos* g8 = &stage.st[w].pos[8 * j];
+            const Aux* x8 = &stage.st[w].aux[8 * j];
             uint32_t pc = (uint32_t)__popcll(mask);
             asm("" : "+s"(pc));  // keeps comparisons of it on the scalar unit, in 32 bits
             if constexpr (COUNT) {
@@ -328,8 +355,12 @@ void k_walk_fwd(WalkArgs a)
                 }
                 const uint64_t om = mask & ~am;
                 if (om) {
-                    write_lane(om_lo, om_hi, om, slot);
-                    open_m |= 1ull << slot;
+                    const uint64_t at_slot = 1ull << slot;
+                    if (__builtin_amdgcn_inverse_ballot_w64(at_slot)) {
+                        om_lo = (uint32_t)om;
+                        om_hi = (uint32_t)(om >> 32);
+                    }
+                    open_m |= at_slot;
                 }
             }
         }
@@ -339,16 +370,31 @@ void k_walk_fwd(WalkArgs a)
         const uint64_t leaf_m = __ballot(meta_leaf(meta)) & open_m;
         const uint64_t push_m = open_m & ~leaf_m;
         const int np = (int)__popcll(push_m);
-        if (sp + np > kStack) {
+        int before = 0, all = np;
+        if constexpr (TEAM > 1) {
+            // the waves' pushes follow each other in the order of their groups
+            if (lane == 0) pushes[turn][w] = (uint32_t)np;
+            __syncthreads();  // also: every wave has read its groups
+            all = 0;
+            for (int u = 0; u < TEAM; ++u) {
+                const int c = (int)pushes[turn][u];
+                if (u < w) before += c;
+                all += c;
+            }
+            before = uni(before);
+            all = uni(all);
+            turn ^= 1;
+        }
+        if (sp + all > kStack) {
             stack_over = true;
         } else {
             if (__builtin_amdgcn_inverse_ballot_w64(push_m)) {
-                const int at = sp + (int)popc_below(push_m);
-                stk_m[w][at] = ((uint64_t)om_hi << 32) | om_lo;
-                stk_gs[w][at] = child;
-                stk_b[w][at] = (uint8_t)((meta_nchild(meta) - 1u) | ((meta_level(meta) + 1u) << 3));
+                const int at = sp + before + (int)popc_below(push_m);
+                stk_m[sw][at] = ((uint64_t)om_hi << 32) | om_lo;
+                stk_gs[sw][at] = child;
+                stk_b[sw][at] = (uint8_t)((meta_nchild(meta) - 1u) | ((meta_level(meta) + 1u) << 3));
             }
-            sp = uni(sp + np);
+            sp = uni(sp + all);
             if constexpr (COUNT) max_sp = max(max_sp, sp);
         }
         for (uint64_t lm = leaf_m & ~__ballot(meta_single(meta)); lm; lm &= lm - 1ull) {
@@ -357,7 +403,7 @@ void k_walk_fwd(WalkArgs a)
             // formed in FP64 from this lane's own position (read again: the leaf is
             // rare, and kept in registers the position would cost the walk occupancy).
             const int src = (int)__builtin_ctzll(lm);
-            const uint32_t f = uni(saux[w][src].first), cnt = uni(saux[w][src].count);
+            const uint32_t f = uni(stage.st[w].aux[src].first), cnt = uni(stage.st[w].aux[src].count);
             const uint64_t om = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)om_lo, src) |
                                 ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)om_hi, src) << 32);
             const volatile double* me = &a.sp[su].x;
@@ -378,7 +424,7 @@ void k_walk_fwd(WalkArgs a)
                 }
             }
         }
-        wave_sync();  // the next step restages the slots and rereads the stack
+        team_sync<TEAM>();  // the next step restages the slots and rereads the stack
         // a step adds up to ~50 terms per lane to the plain partial sums
         if (++since_fold == 2 || sp == 0) {
             since_fold = 0;
@@ -401,6 +447,22 @@ void k_walk_fwd(WalkArgs a)
         ox = tx; oy = ty; oz = tz; op = tp;
     } else {
         ox = tx - cx; oy = ty - cy; oz = tz - cz; op = tp - cp;
+    }
+    if constexpr (TEAM > 1) {
+        // the waves' totals, added in FP64 in the waves' order
+        __syncthreads();  // the staged children are done with
+        stage.total[w][0][lane] = F64 ? (double)ox : (double)tx - (double)cx;
+        stage.total[w][1][lane] = F64 ? (double)oy : (double)ty - (double)cy;
+        stage.total[w][2][lane] = F64 ? (double)oz : (double)tz - (double)cz;
+        stage.total[w][3][lane] = F64 ? (double)op : (double)tp - (double)cp;
+        __syncthreads();
+        if (w > 0) return;
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int u = 0; u < TEAM; ++u)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[c] += stage.total[u][c][lane];
+        ox = (R)v[0]; oy = (R)v[1]; oz = (R)v[2]; op = (R)v[3];
     }
     const R Gc = (R)a.G;
     ox *= Gc; oy *= Gc; oz *= Gc; op *= Gc;
@@ -445,16 +507,26 @@ void k_walk_fwd(WalkArgs a)
 
 }  // namespace
 
-void launch_walk_forward(const WalkArgs& a, tc_walk mode, bool count, hipStream_t s)
+// Walk times in us, team / one wavefront (Plummer, theta = 0.5 unless said):
+//   F32C  131072: 246 / 477    262144: 411 / 551    524288: 742 / 804
+//         1000000: 1341 / 1396, theta = 1: 482 / 432    4000000: 5750 / 4880
+//   FP64  262144: 656 / 853    1000000: 2283 / 2405    2000000: 4746 / 4549
+bool walk_team(int64_t n, tc_walk mode) { return n <= (mode == TC_WALK_F64 ? 3 << 18 : 1 << 19); }
+
+void launch_walk_forward(const WalkArgs& a, tc_walk mode, bool count, bool team, hipStream_t s)
 {
     if (a.n == 0) return;
-    const unsigned blocks = (unsigned)((walk_waves(a.n) + kFwdWaves - 1) / kFwdWaves);
+    const int64_t waves = walk_waves(a.n);
+    if (count) team = false;
+    const unsigned blocks = (unsigned)(team ? waves : (waves + kFwdWaves - 1) / kFwdWaves);
     if (mode == TC_WALK_F64) {
-        if (count) k_walk_fwd<true, true><<<blocks, kFwdThreads, 0, s>>>(a);
-        else k_walk_fwd<true, false><<<blocks, kFwdThreads, 0, s>>>(a);
+        if (count) k_walk_fwd<true, true, 1><<<blocks, kFwdThreads, 0, s>>>(a);
+        else if (team) k_walk_fwd<true, false, kFwdWaves><<<blocks, kFwdThreads, 0, s>>>(a);
+        else k_walk_fwd<true, false, 1><<<blocks, kFwdThreads, 0, s>>>(a);
     } else {
-        if (count) k_walk_fwd<false, true><<<blocks, kFwdThreads, 0, s>>>(a);
-        else k_walk_fwd<false, false><<<blocks, kFwdThreads, 0, s>>>(a);
+        if (count) k_walk_fwd<false, true, 1><<<blocks, kFwdThreads, 0, s>>>(a);
+        else if (team) k_walk_fwd<false, false, kFwdWaves><<<blocks, kFwdThreads, 0, s>>>(a);
+        else k_walk_fwd<false, false, 1><<<blocks, kFwdThreads, 0, s>>>(a);
     }
 }
 

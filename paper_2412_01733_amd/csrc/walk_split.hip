@@ -372,30 +372,22 @@ void launch_split(const WalkArgs& a, tc_walk mode, hipStream_t s)
 
 }  // namespace
 
-// Where the lines lie (walk times in us on one MI355X, Plummer, theta = 0.5,
-// T = 8 / 16 / 64):
-//   F32C  32768: 95 / 118 / 413     49152: 143 / 135 / 439    131072: 300 / 262 / 482
-//         262144: 575 / 469 / 548   524288: 1136 / 898 / 813
-//   FP64  65536: 225 / 216 / 510    262144: 845 / 718 / 839
-//         524288: 1694 / 1415 / 1450    1000000: 3273 / 2704 / 2375
-// The FP64 term costs about twice the FP32 one and the staging the same, so the
-// better-filled lanes of 16 targets pay for longer there.
+// Where the lines lie (walk times in us on one MI355X, Plummer, theta = 0.5; T = 8 /
+// T = 16 / a team of four wavefronts for 64 targets, see walk_forward.hip):
+//   F32C  32768: 95 / 118 / 145    49152: 143 / 135 / -    65536: 169 / 155 / 185
+//         131072: 300 / 262 / 246  262144: 575 / 469 / 411
+//   FP64  65536: 225 / 216 / 231   262144: 845 / 718 / 656
 int walk_targets(int64_t n, tc_walk mode)
 {
     if (n <= 5 << 13) return 8;
-    return n <= (mode == TC_WALK_F64 ? 1 << 19 : 3 << 17) ? 16 : 64;
+    return n <= (mode == TC_WALK_F64 ? 1 << 17 : 3 << 15) ? 16 : 64;
 }
 
 // The adjoint adds to a node's gradient with four atomics per wavefront and node,
-// so fewer targets a wavefront mean more atomics (us, T = 8 / 16 / 64):
-//   F32C  1000: 62 / 85 / 361    16384: 242 / 177 / 727    65536: 804 / 576 / 868
-//         131072: 1396 / 1037 / 1004
-//   FP64  16384: 225 / 205 / 885    131072: 1501 / 1136 / 1317    262144: 2912 / 1846 / 2030
-int adjoint_targets(int64_t n, tc_walk mode)
-{
-    if (n <= 4096) return 8;
-    return n <= (mode == TC_WALK_F64 ? 1 << 18 : 3 << 15) ? 16 : 64;
-}
+// so fewer targets a wavefront mean more atomics (us, T = 8 / 16 / team):
+//   F32C  8192: 128 / 144 / 205    16384: 242 / 238 / 227    65536: 880 / 667 / 337
+//   FP64  8192: 129 / 168 / -      16384: 225 / 271 / 263    65536: - / 743 / 499
+int adjoint_targets(int64_t n, tc_walk mode) { return n <= (mode == TC_WALK_F64 ? 1 << 14 : 3 << 12) ? 8 : 64; }
 
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s)
 {
@@ -404,11 +396,10 @@ void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t
     else launch_split<16, false>(a, mode, s);
 }
 
-void launch_walk_split_adjoint(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s)
+void launch_walk_split_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s)
 {
     if (a.n == 0) return;
-    if (targets == 8) launch_split<8, true>(a, mode, s);
-    else launch_split<16, true>(a, mode, s);
+    launch_split<8, true>(a, mode, s);
 }
 
 }  // namespace tc

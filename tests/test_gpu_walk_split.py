@@ -1,5 +1,5 @@
-"""The walks with 8 or 16 targets a wavefront (small inputs, no counting, no
-stored lists) against the FP64 oracle, at sizes around one wavefront's targets,
+"""The walks with 8 or 16 targets a wavefront or a team of wavefronts for 64
+targets (no counting, no stored lists) against the FP64 oracle, at sizes around one wavefront's targets,
 with multi-particle leaves, the direct sum, and on both sides of the sizes at
 which the library changes the number of targets (there against the 64-target
 walk, which the counting walk always uses: the decisions are the same, so the
@@ -64,8 +64,9 @@ def test_split_walks_match_oracle(name, make, theta, eps, walk):
     assert abs(st["sum_m_abs_a"] / (md * np.linalg.norm(ra, axis=1)).sum() - 1) < 1e-6
 
 
-@pytest.mark.parametrize("walk,n", [("f32c", 40960), ("f32c", 40961), ("f32c", 393216), ("f32c", 393217),
-                                    ("f64", 40961), ("f64", 524288), ("f64", 524289)])
+@pytest.mark.parametrize("walk,n", [("f32c", 40960), ("f32c", 40961), ("f32c", 98304), ("f32c", 98305), ("f32c", 524288),
+                                    ("f32c", 524289), ("f64", 40961), ("f64", 131072), ("f64", 131073), ("f64", 786432),
+                                    ("f64", 786433)])
 def test_both_sides_of_the_lines(walk, n):
     import paper_2412_01733_amd as tc
     print("case", walk, n, flush=True)
@@ -110,3 +111,36 @@ def test_wide_walk_matches_oracle(name, walk):
     check_errors(rel_err(pot.cpu().numpy(), rp), walk, counts == nint, "pot")
     again, _, _ = tc.forces(p, mm, theta, eps, walk=walk, count=True)
     assert torch.equal(acc, again)
+
+
+@pytest.mark.parametrize("walk,n", [("f32c", 12288), ("f32c", 12289), ("f32c", 300007), ("f32c", 1048576), ("f32c", 1048577),
+                                    ("f64", 16384), ("f64", 16385), ("f64", 393216), ("f64", 393217)])
+@pytest.mark.parametrize("name", ["plummer", "clumps", "dups"])
+def test_wide_adjoint_matches_replay(name, walk, n):
+    """The adjoint walks against the replay of stored lists on the same
+    tree (another kernel, the same terms): they may differ by rounding and, in
+    F32C, by nothing else, since the decisions are the same."""
+    import paper_2412_01733_amd as tc
+    print("case", name, walk, n, flush=True)
+    g = np.random.default_rng(n)
+    eps = 0.01
+    if name == "plummer":
+        pos, m = workloads.plummer(n, 3, mass=workloads.lognormal_masses(n, 4))
+    elif name == "clumps":
+        pos, m = workloads.clumps(n // 8 + 1, np.array([[x, y, z] for x in (0, 3) for y in (0, 5) for z in (0, 9)], float), 0.02, 5)
+        pos[::50] += g.normal(0, 4.0, pos[::50].shape)
+    else:
+        pos, m = _dups(n, 8)
+        k = g.permutation(n)[:n // 20]
+        pos[k] = pos[:400][g.integers(0, 400, len(k))]
+    p, mm = _gpu(pos, m)
+    n = len(pos)
+    dt = torch.float32 if walk == "f32c" else torch.float64
+    ga, gp = (torch.from_numpy(g.standard_normal(s)).to(p.device, dt) for s in ((n, 3), n))
+    acc, pot, tree = tc.forces(p, mm, 0.7, eps, walk=walk, store_lists=True)
+    assert tree.stats()["lists_stored"]
+    rx, rm = tree.backward(ga, gp)
+    a2, p2 = tree.forces(0.7, eps, walk=walk)
+    gx, gm = tree.backward(ga, gp)
+    for what, a, b in (("acc", a2, acc), ("pot", p2, pot), ("dL/dx", gx, rx), ("dL/dm", gm, rm)):
+        check_errors(rel_err(a.cpu().numpy(), b.cpu().numpy()), walk, what=what, per_target=False)
