@@ -6,7 +6,7 @@
 namespace tc {
 namespace {
 
-constexpr int kDiagThreads = 256;
+constexpr int kDiagThreads = 512;
 
 // Sum of rows [b*chunk, (b+1)*chunk) of a [nw, 4] array into out[b, 4], in a
 // fixed order (thread-strided partial sums, then a fixed tree).
@@ -58,6 +58,8 @@ __global__ __launch_bounds__(256) void k_scatter_counts(const uint32_t* __restri
 }  // namespace
 
 constexpr int64_t kDiagChunk = 2048;
+// up to here one workgroup adds all rows (5 us; a second launch costs as much)
+constexpr int64_t kDiagLone = 8192;
 
 size_t diag_temp_bytes(int64_t nwaves)
 {
@@ -67,8 +69,11 @@ size_t diag_temp_bytes(int64_t nwaves)
 
 void launch_diag_final(const double* part, int64_t nwaves, void* temp, double* out4, hipStream_t s)
 {
-    int64_t nb = (nwaves + kDiagChunk - 1) / kDiagChunk;
-    if (nb < 1) nb = 1;
+    if (nwaves <= kDiagLone) {
+        k_diag_reduce<<<1, kDiagThreads, 0, s>>>(part, nwaves, nwaves, out4);
+        return;
+    }
+    const int64_t nb = (nwaves + kDiagChunk - 1) / kDiagChunk;
     double* mid = (double*)temp;
     k_diag_reduce<<<(unsigned)nb, kDiagThreads, 0, s>>>(part, nwaves, kDiagChunk, mid);
     k_diag_reduce<<<1, kDiagThreads, 0, s>>>(mid, nb, nb, out4);
