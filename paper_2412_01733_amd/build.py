@@ -21,7 +21,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libtreecode.so")
 BUILD_DIR = os.path.join(os.path.dirname(HERE), "_build")
 
-SOURCES = ["keys.hip", "scan.hip", "sort.hip", "sort_small.hip", "build.hip", "moments.hip", "order.hip", "walk.hip", "walk_forward.hip", "walk_adjoint.hip", "walk_split.hip", "adjoint.hip", "diag.hip",
+SOURCES = ["keys.hip", "scan.hip", "sort.hip", "sort_small.hip", "build.hip", "moments.hip", "order.hip", "walk.hip", "walk_forward.hip", "walk_adjoint.hip", "walk_split.hip", "walk_direct.hip", "adjoint.hip", "diag.hip",
            "integrate.hip", "capi.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

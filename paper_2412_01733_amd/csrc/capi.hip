@@ -427,7 +427,8 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
     // Lists are kept only while they fit the budget; otherwise the adjoint re-walks.
     const bool store = (flags & TC_STORE_LISTS) != 0 &&
                        (uint64_t)walk_waves(n) * kListCap * sizeof(uint4) <= kListMaxBytes;
-    const int targets = t->counted || store ? 64 : walk_targets(n, mode);
+    const bool direct = !t->counted && !store && direct_serves(theta, t->host->level_hist[kLevels + 1]);
+    const int targets = t->counted || store || direct ? 64 : walk_targets(n, mode);
     const int64_t waves = (n + targets - 1) / targets;
     TC_TRY(ensure(t, t->diag_part, (size_t)waves * 4 * sizeof(double), s));
     TC_TRY(ensure(t, t->diag_temp, diag_temp_bytes(waves), s));
@@ -451,7 +452,8 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
 
     if (t->counted) launch_fill_u32((uint32_t*)t->visits, 2 * kNumVisitCounters, 0u, s);
     stage_begin(t, kStWalk, s);
-    if (targets < 64) launch_walk_split(a, targets, mode, s);
+    if (direct) launch_direct(a, mode, s);
+    else if (targets < 64) launch_walk_split(a, targets, mode, s);
     else if (store) launch_walk(a, mode, t->counted, s);
     else launch_walk_forward(a, mode, t->counted, walk_team(n, mode), s);
     stage_end(t, kStWalk, s);

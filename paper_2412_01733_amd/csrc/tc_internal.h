@@ -166,6 +166,10 @@ void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 // walk_adjoint.hip: the adjoint walk where no lists are stored
 void launch_walk_adjoint_wide(const WalkArgs& a, tc_walk mode, bool team, hipStream_t s);
 
+// walk_direct.hip: the direct sum, for theta = 0 and no multi-particle leaves
+bool direct_serves(double theta, int64_t multi_leaves);
+void launch_direct(const WalkArgs& a, tc_walk mode, hipStream_t s);
+
 // walk_split.hip: the same walks with 8 or 16 targets a wavefront (the adjoint: 8).
 // Targets a wavefront for n particles, and, of 64, whether a team of wavefronts takes them.
 int walk_targets(int64_t n, tc_walk mode);

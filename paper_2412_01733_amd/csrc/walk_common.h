@@ -207,5 +207,37 @@ __device__ inline uint32_t popc_below(uint64_t m)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// The outputs of a wavefront's targets (lanes with `valid`; su: sorted position),
+// scaled by G, in the caller's order, and its row of the momentum diagnostic:
+// sum m a, sum m |a| in FP64.
+template <typename R>
+__device__ inline void write_target(const WalkArgs& a, const bool valid, const uint32_t su, R ox, R oy, R oz, R op,
+                                    const int64_t row, const uint32_t lane)
+{
+    const R G = (R)a.G;
+    ox *= G; oy *= G; oz *= G; op *= G;
+    double dm[4] = {0.0, 0.0, 0.0, 0.0};
+    if (valid) {
+        const uint32_t i = a.perm[su];
+        R* acc = (R*)a.acc;
+        acc[3 * (int64_t)i + 0] = ox;
+        acc[3 * (int64_t)i + 1] = oy;
+        acc[3 * (int64_t)i + 2] = oz;
+        if (a.pot) ((R*)a.pot)[i] = op;
+        const double m = a.sp[su].m;
+        const double ex = (double)ox, ey = (double)oy, ez = (double)oz;
+        dm[0] = m * ex;
+        dm[1] = m * ey;
+        dm[2] = m * ez;
+        dm[3] = m * sqrt(ex * ex + ey * ey + ez * ez);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dm[k] = wave_sum(dm[k]);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a.diag[4 * row + k] = dm[k];
+    }
+}
+
 }  // namespace
 }  // namespace tc

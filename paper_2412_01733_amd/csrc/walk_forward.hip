@@ -464,31 +464,10 @@ void k_walk_fwd(WalkArgs a)
             for (int c = 0; c < 4; ++c) v[c] += stage.total[u][c][lane];
         ox = (R)v[0]; oy = (R)v[1]; oz = (R)v[2]; op = (R)v[3];
     }
-    const R Gc = (R)a.G;
-    ox *= Gc; oy *= Gc; oz *= Gc; op *= Gc;
-
-    double dm[4] = {0.0, 0.0, 0.0, 0.0};
-    if (valid) {
-        const uint32_t i = a.perm[su];
-        R* acc = (R*)a.acc;
-        acc[3 * (int64_t)i + 0] = ox;
-        acc[3 * (int64_t)i + 1] = oy;
-        acc[3 * (int64_t)i + 2] = oz;
-        if (a.pot) ((R*)a.pot)[i] = op;
-        if constexpr (COUNT) a.counts[su] = nint;
-        const double m = a.sp[su].m;
-        const double ex = (double)ox, ey = (double)oy, ez = (double)oz;
-        dm[0] = m * ex;
-        dm[1] = m * ey;
-        dm[2] = m * ez;
-        dm[3] = m * sqrt(ex * ex + ey * ey + ez * ez);
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) dm[k] = wave_sum(dm[k]);
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) a.diag[4 * wave_id + k] = dm[k];
-        if constexpr (COUNT) {
+    write_target<R>(a, valid, su, ox, oy, oz, op, wave_id, lane);
+    if constexpr (COUNT) {
+        if (valid) a.counts[su] = nint;
+        if (lane == 0) {
             atomicAdd(&a.visits[0], (unsigned long long)vis_nodes);
             atomicAdd(&a.visits[1], (unsigned long long)vis_lanes);
             atomicAdd(&a.visits[2], (unsigned long long)vis_groups);

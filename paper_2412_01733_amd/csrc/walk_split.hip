@@ -336,28 +336,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
             tg[0] = v[0]; tg[1] = v[1]; tg[2] = v[2];
         }
     } else {
-        double dm[4] = {0.0, 0.0, 0.0, 0.0};
-        if (valid && s == 0) {
-            const R ox = (R)v[0] * Gc, oy = (R)v[1] * Gc, oz = (R)v[2] * Gc, op = (R)v[3] * Gc;
-            const uint32_t i = a.perm[su];
-            R* acc = (R*)a.acc;
-            acc[3 * (int64_t)i + 0] = ox;
-            acc[3 * (int64_t)i + 1] = oy;
-            acc[3 * (int64_t)i + 2] = oz;
-            if (a.pot) ((R*)a.pot)[i] = op;
-            const double m = self.m;
-            const double ex = (double)ox, ey = (double)oy, ez = (double)oz;
-            dm[0] = m * ex;
-            dm[1] = m * ey;
-            dm[2] = m * ez;
-            dm[3] = m * sqrt(ex * ex + ey * ey + ez * ez);
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) dm[k] = wave_sum(dm[k]);
-        if (lane == 0) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a.diag[4 * wave_id + k] = dm[k];
-        }
+        write_target<R>(a, valid && s == 0, su, (R)v[0], (R)v[1], (R)v[2], (R)v[3], wave_id, lane);
     }
 }
 

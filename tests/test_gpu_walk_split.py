@@ -144,3 +144,32 @@ def test_wide_adjoint_matches_replay(name, walk, n):
     gx, gm = tree.backward(ga, gp)
     for what, a, b in (("acc", a2, acc), ("pot", p2, pot), ("dL/dx", gx, rx), ("dL/dm", gm, rm)):
         check_errors(rel_err(a.cpu().numpy(), b.cpu().numpy()), walk, what=what, per_target=False)
+
+
+@pytest.mark.parametrize("walk", ["f32c", "f64"])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1024, 1025, 4099])
+def test_direct_kernel_matches_oracle(n, walk):
+    """theta = 0 around a block's targets, a run of sources and the 16 runs of a block."""
+    import paper_2412_01733_amd as tc
+    pos, m = workloads.plummer(n, 70 + n)
+    p, mm = _gpu(pos, m)
+    acc, pot, _ = tc.forces(p, mm, 0.0, 0.01, walk=walk)
+    if n == 1:
+        assert (acc == 0).all() and (pot == 0).all()
+        return
+    ra, rp = oracle.direct(pos, m, 0.01)
+    check_errors(rel_err(acc.cpu().numpy(), ra), walk, what="acc")
+    check_errors(rel_err(pot.cpu().numpy(), rp), walk, what="pot")
+
+
+@pytest.mark.parametrize("walk", ["f32c", "f64"])
+def test_direct_sum_with_shared_cells_takes_the_walk(walk):
+    """Leaves of several particles need FP64 separations: theta = 0 then walks."""
+    import paper_2412_01733_amd as tc
+    pos, m = _dups(1500, 6)
+    p, mm = _gpu(pos, m)
+    acc, pot, tree = tc.forces(p, mm, 0.0, 0.001, walk=walk)
+    assert tree.stats()["n_multi_leaves"] > 0
+    ra, rp = oracle.direct(pos, m, 0.001)
+    check_errors(rel_err(acc.cpu().numpy(), ra), walk, what="acc")
+    check_errors(rel_err(pot.cpu().numpy(), rp), walk, what="pot")
