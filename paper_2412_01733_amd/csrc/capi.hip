@@ -483,14 +483,16 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     if (n == 0) return TC_OK;
     TC_TRY(ensure(t, t->node_grad, (size_t)nn * 4 * sizeof(double), s));
     TC_TRY(ensure(t, t->uc, (size_t)nn * 4 * sizeof(double), s));
-    TC_TRY(ensure(t, t->part_grad, (size_t)n * 4 * sizeof(double), s));
+    // direct-term gradients: only particles of leaves that several share receive any
+    const bool multi = t->host->level_hist[kLevels + 1] > 0;
+    if (multi) TC_TRY(ensure(t, t->part_grad, (size_t)n * 4 * sizeof(double), s));
     TC_TRY(ensure(t, t->target_grad, (size_t)n * 3 * sizeof(double), s));
     WalkArgs a{};
     TC_TRY(walk_args(t, t->f_theta, t->f_eps, t->f_G, t->last_mode, a));
     a.g_acc = g_acc;
     a.g_pot = g_pot;
     a.node_grad = P<double>(t->node_grad);
-    a.part_grad = P<double>(t->part_grad);
+    a.part_grad = multi ? P<double>(t->part_grad) : nullptr;
     a.target_grad = P<double>(t->target_grad);
     if (t->lists_stored) {
         a.lists = P<uint4>(t->lists);
@@ -499,7 +501,7 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     }
     stage_begin(t, kStBwdWalk, s);
     launch_fill_f64_zero(a.node_grad, nn * 4, s);
-    launch_fill_f64_zero(a.part_grad, n * 4, s);
+    if (multi) launch_fill_f64_zero(a.part_grad, n * 4, s);
     const int targets = t->lists_stored ? 64 : adjoint_targets(n, t->last_mode);
     if (targets < 64) launch_walk_split_adjoint(a, t->last_mode, s);
     else if (t->lists_stored) launch_walk_adjoint(a, t->last_mode, s);
@@ -509,8 +511,8 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     HIP_TRY(hipMemcpyAsync(&t->host->status, t->status, 4, hipMemcpyDeviceToHost, s));
     t->walk_status_pending = true;
     stage_begin(t, kStBwdDown, s);
-    launch_adjoint_down(t->host->level_off, P<WalkNode>(t->wn), P<uint2>(t->up), a.node_grad, P<double>(t->uc),
-                        a.sp, t->perm, a.target_grad, a.part_grad, g_pos, g_mass,
+    launch_adjoint_down(t->host->level_off, n, P<uint4>(t->topo), P<WalkNode>(t->wn), P<uint2>(t->up), a.node_grad,
+                        P<double>(t->uc), P<uint32_t>(t->leaf_of), a.sp, t->perm, a.target_grad, a.part_grad, g_pos, g_mass,
                         t->last_mode == TC_WALK_F64, s);
     stage_end(t, kStBwdDown, s);
     TC_TRY(check_launch("adjoint down-pass"));

@@ -137,7 +137,7 @@ struct WalkArgs {
     const void* g_acc;      // dL/da [n,3], caller order, walk precision
     const void* g_pot;      // dL/dphi [n] or NULL
     double* node_grad;      // [nodes, 4] breadth-first: dL/dX (3), dL/dM, accumulated
-    double* part_grad;      // [n, 4] sorted order: dL/dx_j (3), dL/dm_j from opened multi-particle leaves
+    double* part_grad;      // [n, 4] sorted order: dL/dx_j (3), dL/dm_j from opened multi-particle leaves; null if there are none
     double* target_grad;    // [n, 3] sorted order: dL/dx_i from the target side
     // stored interaction lists: per wave, in visit order, records {node, kind, lane mask lo, hi};
     // kind 0: the node was accepted by the mask's lanes; kind 1: the multi-particle leaf was
@@ -185,10 +185,10 @@ void launch_target_order(int64_t n, int64_t nn, const uint64_t* skeys, const uin
                          const uint32_t* leaf_of, uint2* up, uint32_t* order, hipStream_t s);
 
 // adjoint.hip: top-down pass from node gradients to particle gradients.
-void launch_adjoint_down(const uint32_t* level_off_host, const WalkNode* wn, const uint2* up,
-                         const double* node_grad, double* uc, const Particle* sp, const uint32_t* perm,
-                         const double* target_grad,
-                         const double* part_grad, void* g_pos, void* g_mass, bool out_f64, hipStream_t s);
+void launch_adjoint_down(const uint32_t* level_off_host, int64_t n, const uint4* topo, const WalkNode* wn, const uint2* up,
+                         const double* node_grad, double* uc, const uint32_t* leaf_of, const Particle* sp,
+                         const uint32_t* perm, const double* target_grad, const double* part_grad, void* g_pos,
+                         void* g_mass, bool out_f64, hipStream_t s);
 void launch_fill_f64_zero(double* p, int64_t n, hipStream_t s);
 
 // integrate.hip: leapfrog pieces and FP64 step diagnostics
