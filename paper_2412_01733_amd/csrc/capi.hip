@@ -7,8 +7,10 @@
 #include <cstddef>
 #include <cstdio>
 #include <cstring>
+#include <initializer_list>
 #include <mutex>
 #include <string>
+#include <vector>
 
 #include "tc_internal.h"
 
@@ -79,14 +81,17 @@ struct tc_tree {
     int64_t nn = 0;
     tc_dtype dtype = TC_F32;
 
+    // Three allocations hold the buffers below them (carve): what a build of n particles
+    // needs, what its nodes need, what a backward pass needs.
+    Buf particle_slab, node_slab, grad_slab;
     // particle-sized
     Buf keys0, keys1, vals0, vals1, rec, sp, leaf_of, sorted_counts, diag_part;
     uint64_t* skeys = nullptr;
     uint32_t* perm = nullptr;
     Buf sort_temp, tree_table, bounds_part;
     // node-sized
-    Buf topo, ends, up, wn, diag_temp;
-    Buf order;                 // the walk's target order (particle-sized)
+    Buf topo, ends, up, wn;
+    Buf order, diag_temp;      // the walk's target order (particle-sized), and its diagnostics' scratch
     // adjoint and leapfrog
     Buf node_grad, uc, part_grad, target_grad, step_temp;
     Buf lists, list_len;       // stored interaction lists of the last tc_forces (TC_STORE_LISTS)
@@ -117,10 +122,23 @@ struct tc_tree {
     hipEvent_t ev[2 * kNumStages] = {};
     bool ev_used[kNumStages] = {};
     hipEvent_t done = nullptr;  // recorded after the last work each call enqueues (tc_tree_free waits on it)
+    bool unmarked = false;      // some call's completion could not be recorded: tc_tree_free waits for the device
     bool walk_status_pending = false;  // a walk's status word is on its way to host->status
 };
 
 namespace {
+
+#define TC_TRY(expr)                          \
+    do {                                      \
+        tc_status _st = (expr);               \
+        if (_st != TC_OK) return _st;         \
+    } while (0)
+
+#define HIP_TRY(expr)                                                                  \
+    do {                                                                               \
+        hipError_t _e = (expr);                                                        \
+        if (_e != hipSuccess) return fail(TC_ERR_DEVICE, "%s: %s", #expr, hipGetErrorString(_e)); \
+    } while (0)
 
 tc_status ensure(tc_tree* t, Buf& b, size_t bytes, hipStream_t s)
 {
@@ -138,6 +156,27 @@ tc_status ensure(tc_tree* t, Buf& b, size_t bytes, hipStream_t s)
     return TC_OK;
 }
 
+// Lays the given buffers out in one allocation (each at a 256-byte boundary).
+// Their contents are lost whenever the allocation has to grow.
+struct Want {
+    Buf* buf;
+    size_t bytes;
+};
+
+tc_status carve(tc_tree* t, Buf& slab, std::initializer_list<Want> wants, hipStream_t s)
+{
+    size_t total = 0;
+    for (const Want& w : wants) total += (w.bytes + 255) & ~(size_t)255;
+    TC_TRY(ensure(t, slab, total, s));
+    char* p = (char*)slab.p;
+    for (const Want& w : wants) {
+        w.buf->p = p;
+        w.buf->bytes = w.bytes;
+        p += (w.bytes + 255) & ~(size_t)255;
+    }
+    return TC_OK;
+}
+
 void release(tc_tree* t, Buf& b)
 {
     if (b.p) t->freef(b.p, nullptr, t->actx);
@@ -147,18 +186,6 @@ void release(tc_tree* t, Buf& b)
 
 template <typename T>
 T* P(const Buf& b) { return (T*)b.p; }
-
-#define TC_TRY(expr)                          \
-    do {                                      \
-        tc_status _st = (expr);               \
-        if (_st != TC_OK) return _st;         \
-    } while (0)
-
-#define HIP_TRY(expr)                                                                  \
-    do {                                                                               \
-        hipError_t _e = (expr);                                                        \
-        if (_e != hipSuccess) return fail(TC_ERR_DEVICE, "%s: %s", #expr, hipGetErrorString(_e)); \
-    } while (0)
 
 tc_status check_launch(const char* what)
 {
@@ -217,6 +244,56 @@ tc_status carve_small(tc_tree* t, hipStream_t s)
     return TC_OK;
 }
 
+// Pinned host mirrors and completion events of freed handles, kept for the next
+// handle on the same device (a differentiable call makes and frees one each time;
+// pinning and unpinning cost 40 us).  A handle returns its pair only once its
+// enqueued work is done.  At most kHostPool of them (1.5 KiB each) are kept.
+struct HostPair {
+    int device;
+    HostMirror* host;
+    hipEvent_t done;
+};
+constexpr size_t kHostPool = 8;
+std::mutex g_host_mu;
+std::vector<HostPair> g_host_pool;
+
+tc_status take_host_pair(int dev, HostPair* out)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_host_mu);
+        for (size_t i = 0; i < g_host_pool.size(); ++i) {
+            if (g_host_pool[i].device != dev) continue;
+            *out = g_host_pool[i];
+            g_host_pool.erase(g_host_pool.begin() + (ptrdiff_t)i);
+            return TC_OK;
+        }
+    }
+    out->device = dev;
+    if (hipHostMalloc((void**)&out->host, sizeof(HostMirror), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(TC_ERR_NOMEM, "pinned host allocation failed");
+    }
+    if (hipEventCreateWithFlags(&out->done, hipEventDisableTiming) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipHostFree(out->host);
+        return fail(TC_ERR_DEVICE, "event creation failed");
+    }
+    return TC_OK;
+}
+
+void give_host_pair(const HostPair& p)
+{
+    {
+        std::lock_guard<std::mutex> lk(g_host_mu);
+        if (g_host_pool.size() < kHostPool) {
+            g_host_pool.push_back(p);
+            return;
+        }
+    }
+    (void)hipEventDestroy(p.done);
+    (void)hipHostFree(p.host);
+}
+
 tc_status create_tree(tc_tree** out, hipStream_t s)
 {
     int dev;
@@ -234,20 +311,16 @@ tc_status create_tree(tc_tree** out, hipStream_t s)
         delete t;
         return st;
     }
-    if (hipHostMalloc((void**)&t->host, sizeof(HostMirror), hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
+    HostPair hp{};
+    st = take_host_pair(dev, &hp);
+    if (st != TC_OK) {
         release(t, t->small);
         delete t;
-        return fail(TC_ERR_NOMEM, "pinned host allocation failed");
+        return st;
     }
-    memset(t->host, 0, sizeof(HostMirror));
-    if (hipEventCreateWithFlags(&t->done, hipEventDisableTiming) != hipSuccess) {
-        (void)hipGetLastError();
-        (void)hipHostFree(t->host);
-        release(t, t->small);
-        delete t;
-        return fail(TC_ERR_DEVICE, "event creation failed");
-    }
+    t->host = hp.host;
+    t->done = hp.done;
+    memset((void*)t->host, 0, sizeof(HostMirror));
     *out = t;
     return TC_OK;
 }
@@ -255,7 +328,10 @@ tc_status create_tree(tc_tree** out, hipStream_t s)
 // Record the handle's completion event after the work a call enqueued on s.
 tc_status mark_done(tc_tree* t, hipStream_t s, tc_status st)
 {
-    if (t && t->done && hipEventRecord(t->done, s) != hipSuccess) (void)hipGetLastError();
+    if (t && t->done && hipEventRecord(t->done, s) != hipSuccess) {
+        (void)hipGetLastError();
+        t->unmarked = true;
+    }
     return st;
 }
 
@@ -304,20 +380,15 @@ tc_status build_impl(tc_tree* t, const void* pos, const void* mass, int64_t n, t
         return TC_OK;
     }
     const size_t n8 = (size_t)n * 8, n4 = (size_t)n * 4;
-    TC_TRY(ensure(t, t->keys0, n8, s));
-    TC_TRY(ensure(t, t->keys1, n8, s));
-    TC_TRY(ensure(t, t->vals0, n4, s));
-    TC_TRY(ensure(t, t->vals1, n4, s));
-    TC_TRY(ensure(t, t->sp, (size_t)n * sizeof(Particle), s));
-    TC_TRY(ensure(t, t->leaf_of, n4, s));
-    TC_TRY(ensure(t, t->tree_table, tree_table_bytes(n), s));
     const bool small = n <= kSortSmall;
     const int nb = small && sort_small_lone(n) ? 0 : bounds_blocks(n);
-    TC_TRY(ensure(t, t->bounds_part, (size_t)nb * 8 * sizeof(double), s));
-    if (!small) {
-        TC_TRY(ensure(t, t->rec, record_bytes(n, dt), s));
-        TC_TRY(ensure(t, t->sort_temp, radix_temp_bytes(n), s));
-    }
+    const int64_t rows = walk_rows_max(n);
+    TC_TRY(carve(t, t->particle_slab,
+                 {{&t->keys0, n8}, {&t->keys1, n8}, {&t->vals0, n4}, {&t->vals1, n4}, {&t->sp, (size_t)n * sizeof(Particle)},
+                  {&t->leaf_of, n4}, {&t->order, n4}, {&t->tree_table, tree_table_bytes(n)},
+                  {&t->bounds_part, (size_t)nb * 8 * sizeof(double)}, {&t->rec, small ? 0 : record_bytes(n, dt)},
+                  {&t->sort_temp, small ? 0 : radix_temp_bytes(n)}, {&t->diag_part, (size_t)rows * 4 * sizeof(double)},
+                  {&t->diag_temp, diag_temp_bytes(rows)}}, s));
 
     stage_begin(t, kStKeys, s);
     if (nb > 0) launch_bounds(pos, mass, n, dt, P<double>(t->bounds_part), nb, small ? nullptr : t->geom, s);
@@ -357,9 +428,9 @@ tc_status build_impl(tc_tree* t, const void* pos, const void* mass, int64_t n, t
     t->host->level_off[kLevels] = (uint32_t)total;
     const int64_t nn = (int64_t)total;
     t->nn = nn;
-    TC_TRY(ensure(t, t->topo, (size_t)nn * sizeof(uint4), s));
-    TC_TRY(ensure(t, t->ends, (size_t)nn * sizeof(uint2), s));
-    TC_TRY(ensure(t, t->wn, (size_t)nn * sizeof(WalkNode), s));
+    TC_TRY(carve(t, t->node_slab,
+                 {{&t->wn, (size_t)nn * sizeof(WalkNode)}, {&t->topo, (size_t)nn * sizeof(uint4)},
+                  {&t->ends, (size_t)nn * sizeof(uint2)}, {&t->up, (size_t)nn * sizeof(uint2)}}, s));
 
     launch_emit(t->skeys, n, P<uint32_t>(t->tree_table), t->host->level_off, P<Particle>(t->sp), P<uint4>(t->topo),
                 P<uint2>(t->ends), P<WalkNode>(t->wn), P<uint32_t>(t->leaf_of), t->status, s);
@@ -373,8 +444,6 @@ tc_status moments_impl(tc_tree* t, hipStream_t s)
 {
     if (t->n > 0) {
         stage_begin(t, kStMoments, s);
-        TC_TRY(ensure(t, t->up, (size_t)t->nn * sizeof(uint2), s));
-        TC_TRY(ensure(t, t->order, (size_t)t->n * 4, s));
         launch_moments(t->host->level_off, P<uint4>(t->topo), P<uint2>(t->ends), t->skeys, P<Particle>(t->sp), t->geom,
                        P<WalkNode>(t->wn), s);
         launch_target_order(t->n, t->nn, t->skeys, P<uint4>(t->topo), P<uint2>(t->ends), P<uint32_t>(t->leaf_of),
@@ -430,8 +499,6 @@ tc_status forces_impl(tc_tree* t, double theta, double eps, double G, tc_walk mo
     const bool direct = !t->counted && !store && direct_serves(theta, t->host->level_hist[kLevels + 1]);
     const int targets = t->counted || store || direct ? 64 : walk_targets(n, mode);
     const int64_t waves = (n + targets - 1) / targets;
-    TC_TRY(ensure(t, t->diag_part, (size_t)waves * 4 * sizeof(double), s));
-    TC_TRY(ensure(t, t->diag_temp, diag_temp_bytes(waves), s));
     if (t->counted) TC_TRY(ensure(t, t->sorted_counts, (size_t)n * 4, s));
 
     WalkArgs a{};
@@ -481,12 +548,12 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
 {
     const int64_t n = t->n, nn = t->nn;
     if (n == 0) return TC_OK;
-    TC_TRY(ensure(t, t->node_grad, (size_t)nn * 4 * sizeof(double), s));
-    TC_TRY(ensure(t, t->uc, (size_t)nn * 4 * sizeof(double), s));
     // direct-term gradients: only particles of leaves that several share receive any
     const bool multi = t->host->level_hist[kLevels + 1] > 0;
-    if (multi) TC_TRY(ensure(t, t->part_grad, (size_t)n * 4 * sizeof(double), s));
-    TC_TRY(ensure(t, t->target_grad, (size_t)n * 3 * sizeof(double), s));
+    TC_TRY(carve(t, t->grad_slab,
+                 {{&t->node_grad, (size_t)nn * 4 * sizeof(double)}, {&t->uc, (size_t)nn * 4 * sizeof(double)},
+                  {&t->target_grad, (size_t)n * 3 * sizeof(double)}, {&t->part_grad, multi ? (size_t)n * 4 * sizeof(double) : 0}},
+                 s));
     WalkArgs a{};
     TC_TRY(walk_args(t, t->f_theta, t->f_eps, t->f_G, t->last_mode, a));
     a.g_acc = g_acc;
@@ -884,16 +951,17 @@ void tc_tree_free(tc_tree* t)
 {
     if (!t) return;
     // wait for the work the handle's calls enqueued (on whichever stream), not the whole device
-    if (t->done && hipEventSynchronize(t->done) != hipSuccess) (void)hipGetLastError();
-    Buf* bufs[] = {&t->keys0, &t->keys1, &t->vals0, &t->vals1, &t->rec, &t->sp, &t->leaf_of, &t->sorted_counts,
-                   &t->diag_part, &t->sort_temp, &t->tree_table, &t->bounds_part, &t->topo, &t->ends, &t->up, &t->wn,
-                   &t->diag_temp, &t->order, &t->node_grad, &t->uc, &t->part_grad, &t->target_grad, &t->step_temp,
-                   &t->lists, &t->list_len, &t->small};
+    if (t->done && hipEventSynchronize(t->done) != hipSuccess) {
+        (void)hipGetLastError();
+        t->unmarked = true;
+    }
+    if (t->unmarked && hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
+    Buf* bufs[] = {&t->particle_slab, &t->node_slab, &t->grad_slab, &t->sorted_counts, &t->step_temp, &t->lists, &t->list_len,
+                   &t->small};
     for (Buf* b : bufs) release(t, *b);
     for (auto& e : t->ev)
         if (e) (void)hipEventDestroy(e);
-    if (t->done) (void)hipEventDestroy(t->done);
-    if (t->host) (void)hipHostFree(t->host);
+    if (t->host) give_host_pair({t->device, t->host, t->done});
     delete t;
 }
 

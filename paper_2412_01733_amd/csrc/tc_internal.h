@@ -173,6 +173,7 @@ void launch_direct(const WalkArgs& a, tc_walk mode, hipStream_t s);
 // walk_split.hip: the same walks with 8 or 16 targets a wavefront (the adjoint: 8).
 // Targets a wavefront for n particles, and, of 64, whether a team of wavefronts takes them.
 int walk_targets(int64_t n, tc_walk mode);
+int64_t walk_rows_max(int64_t n);  // diagnostic rows (wavefronts) of any walk of n particles at most
 bool walk_team(int64_t n, tc_walk mode);
 int adjoint_targets(int64_t n, tc_walk mode);
 bool adjoint_team(int64_t n, tc_walk mode);

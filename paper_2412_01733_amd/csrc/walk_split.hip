@@ -362,6 +362,12 @@ int walk_targets(int64_t n, tc_walk mode)
     return n <= (mode == TC_WALK_F64 ? 1 << 17 : 3 << 15) ? 16 : 64;
 }
 
+int64_t walk_rows_max(int64_t n)
+{
+    const int t = min(walk_targets(n, TC_WALK_F32C), walk_targets(n, TC_WALK_F64));
+    return (n + t - 1) / t;
+}
+
 // The adjoint adds to a node's gradient with four atomics per wavefront and node,
 // so fewer targets a wavefront mean more atomics (us, T = 8 / 16 / team):
 //   F32C  8192: 128 / 144 / 205    16384: 242 / 238 / 227    65536: 880 / 667 / 337
