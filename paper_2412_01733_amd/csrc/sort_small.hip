@@ -1,7 +1,8 @@
 // Keys, sort and gather for inputs that a radix sort's passes do not pay for.
 //
-// An 8-bit pass of sort.hip costs three launches, and eight passes are needed
-// whatever n is: 25 us each below 1e5 particles, whose data fit in the L2s.
+// A pass of sort.hip costs three launches, and seven passes are needed whatever
+// n is (keys, sort and gather: 120 us at 1.3e5 particles, against 92 here; 140 and
+// 125 at 4e5; 150 and 138 at 5.2e5; 183 and 248 at 8e5).
 // Here one launch computes the keys of tiles of 2048 particles and sorts each
 // tile in LDS; then every launch merges up to 8 neighbouring runs by rank: a
 // key's place is its own place in its run plus the number of keys before it in

@@ -25,6 +25,8 @@ def _dups(n, seed):
 
 CASES = [(n, "plummer") for n in (1023, 1024, 1025, 2047, 2048, 2049, 4097, 16384, 16385, 131073, 524288, 524289)]
 CASES += [(n, "dups") for n in (2050, 20000, 140001, 600001)]
+# the radix sort's tiles change from 2048 to 3072 keys at 5 * 2^18 (whole tiles, a tail of one key, eighths of unequal length)
+CASES += [(1310719, "plummer"), (1310720, "plummer"), (1310721, "dups"), (3072 * 431, "plummer")]
 
 
 @pytest.mark.parametrize("n,kind", CASES)
