@@ -29,16 +29,10 @@
 namespace tc {
 namespace {
 
-constexpr int kTreeThreads = 1024;  // a particle each
+constexpr int kTreeThreads = kTreeBlock;  // a particle each
 constexpr int kTreeWaves = kTreeThreads / 64;
 
 inline unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
-
-__device__ inline int shared_level(uint64_t a, uint64_t b)
-{
-    const uint64_t x = a ^ b;
-    return x ? (__clzll((long long)x) - 1) / 3 : kMaxLevel;
-}
 
 // c_{s-1}, c_s and m_s of particle s.
 struct Span {

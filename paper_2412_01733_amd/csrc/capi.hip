@@ -444,7 +444,7 @@ tc_status moments_impl(tc_tree* t, hipStream_t s)
 {
     if (t->n > 0) {
         stage_begin(t, kStMoments, s);
-        launch_moments(t->host->level_off, P<uint4>(t->topo), P<uint2>(t->ends), t->skeys, P<Particle>(t->sp), t->geom,
+        launch_moments(t->n, P<uint32_t>(t->tree_table), t->host->level_off, P<uint4>(t->topo), P<uint2>(t->ends), t->skeys, P<Particle>(t->sp), t->geom,
                        P<WalkNode>(t->wn), s);
         launch_target_order(t->n, t->nn, t->skeys, P<uint4>(t->topo), P<uint2>(t->ends), P<uint32_t>(t->leaf_of),
                             P<uint2>(t->up), P<uint32_t>(t->order), s);

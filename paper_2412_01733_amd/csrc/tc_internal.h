@@ -52,6 +52,7 @@ struct LevelOffsets {
     uint32_t off[kLevels + 1];
     __host__ __device__ uint32_t size(int l) const { return off[l + 1] - off[l]; }
 };
+constexpr int kTreeBlock = 1024;  // particles a column of the tree's table
 constexpr uint32_t kSmallLevel = 4096;
 constexpr int kSmallLevelThreads = 1024;
 
@@ -62,6 +63,13 @@ __host__ __device__ inline bool meta_single(uint32_t m) { return (m >> 17) & 1u;
 __host__ __device__ inline uint32_t meta_octant(uint32_t m) { return (m >> 18) & 7u; }
 // level + 32 * single (bit 13 repeats the single flag): the walk's threshold table index
 __host__ __device__ inline uint32_t meta_tau_index(uint32_t m) { return (m >> 8) & 0x3Fu; }
+
+// Deepest level at which two keys share a cell.
+__device__ inline int shared_level(uint64_t a, uint64_t b)
+{
+    const uint64_t x = a ^ b;
+    return x ? (__clzll((long long)x) - 1) / 3 : kMaxLevel;
+}
 
 // ---------------------------------------------------------------------------
 // launch wrappers (each defined next to its kernels)
@@ -111,9 +119,8 @@ void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table
                          const uint2* ends, const WalkNode* wn, int64_t nn, uint8_t* level, uint32_t* first,
                          uint32_t* count, double* com, double* mass, hipStream_t s);
 
-// moments.hip: one launch per level over the breadth-first ranges
-// [level_off_host[l], level_off_host[l+1]), deepest level first.
-void launch_moments(const uint32_t* level_off_host, const uint4* topo, const uint2* ends, const uint64_t* skeys,
+// moments.hip: the upward pass.  table as launch_tree_counts left it.
+void launch_moments(int64_t n, const uint32_t* table, const uint32_t* level_off_host, const uint4* topo, const uint2* ends, const uint64_t* skeys,
                     const Particle* sp, const Geom* geom, WalkNode* wn, hipStream_t s);
 
 // walk.hip

@@ -28,6 +28,11 @@ CASES += [(n, "dups") for n in (2050, 20000, 140001, 600001)]
 # the radix sort's tiles change from 2048 to 3072 keys at 5 * 2^18 (whole tiles, a tail of one key, eighths of unequal length)
 CASES += [(1310719, "plummer"), (1310720, "plummer"), (1310721, "dups"), (3072 * 431, "plummer")]
 
+# the upward pass: the whole tree in one workgroup up to 4096 particles, parts of 1024 up to 2^18, of 2048 up to
+# 5 * 2^17, level by level above (leaves and nodes that cross parts, a lone particle in the last part)
+CASES += [(n, k) for n in (4096, 262144, 262145, 655360, 655361) for k in ("plummer", "dups")]
+CASES += [(2, "plummer"), (1025, "dups"), (3073, "dups"), (260097, "plummer"), (264193, "dups")]
+
 
 @pytest.mark.parametrize("n,kind", CASES)
 def test_tables_match_oracle(n, kind):
