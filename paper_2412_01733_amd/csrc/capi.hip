@@ -569,7 +569,7 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     stage_begin(t, kStBwdWalk, s);
     launch_fill_f64_zero(a.node_grad, nn * 4, s);
     if (multi) launch_fill_f64_zero(a.part_grad, n * 4, s);
-    const int targets = t->lists_stored ? 64 : adjoint_targets(n, t->last_mode);
+    const int targets = t->lists_stored ? 64 : adjoint_targets(n);
     if (targets < 64) launch_walk_split_adjoint(a, t->last_mode, s);
     else if (t->lists_stored) launch_walk_adjoint(a, t->last_mode, s);
     else launch_walk_adjoint_wide(a, t->last_mode, adjoint_team(n, t->last_mode), s);

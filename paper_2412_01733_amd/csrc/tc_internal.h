@@ -171,7 +171,7 @@ void launch_walk_forward(const WalkArgs& a, tc_walk mode, bool count, bool team,
 // adjoint walk: replays stored lists, or walks for the wavefronts that have none
 void launch_walk_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 // walk_adjoint.hip: the adjoint walk where no lists are stored
-void launch_walk_adjoint_wide(const WalkArgs& a, tc_walk mode, bool team, hipStream_t s);
+void launch_walk_adjoint_wide(const WalkArgs& a, tc_walk mode, int team, hipStream_t s);
 
 // walk_direct.hip: the direct sum, for theta = 0 and no multi-particle leaves
 bool direct_serves(double theta, int64_t multi_leaves);
@@ -182,8 +182,8 @@ void launch_direct(const WalkArgs& a, tc_walk mode, hipStream_t s);
 int walk_targets(int64_t n, tc_walk mode);
 int64_t walk_rows_max(int64_t n);  // diagnostic rows (wavefronts) of any walk of n particles at most
 bool walk_team(int64_t n, tc_walk mode);
-int adjoint_targets(int64_t n, tc_walk mode);
-bool adjoint_team(int64_t n, tc_walk mode);
+int adjoint_targets(int64_t n);
+int adjoint_team(int64_t n, tc_walk mode);  // wavefronts for 64 targets
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s);
 void launch_walk_split_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 

@@ -21,10 +21,10 @@ namespace tc {
 namespace {
 
 constexpr int kAdjWaves = 4;
-constexpr int kAdjThreads = 64 * kAdjWaves;
+constexpr int block_waves(int team) { return team > 1 ? team : kAdjWaves; }  // a team is a block
 constexpr uint32_t kXcdRun = 64;  // consecutive blocks one XCD takes at a time
 
-// (a team: see walk_forward.hip)
+// A team: see walk_forward.hip; its wavefronts are the block, 4, 8 or 16 of them.
 constexpr int kTeamStack = 400;
 
 // groups a step, stack entries (the bound of walk_forward.hip), wavefronts per SIMD
@@ -37,14 +37,13 @@ template <bool F64> struct AdjShape {
 };
 
 template <bool F64, int TEAM>
-__global__ __launch_bounds__(kAdjThreads) __attribute__((amdgpu_waves_per_eu(AdjShape<F64>::waves)))
+__global__ __launch_bounds__(64 * block_waves(TEAM)) __attribute__((amdgpu_waves_per_eu(AdjShape<F64>::waves)))
 void k_walk_adj(WalkArgs a)
 {
     using R = typename std::conditional<F64, double, float>::type;
     using Shape = AdjShape<F64>;
     constexpr int kGroups = Shape::groups, kStack = TEAM > 1 ? kTeamStack : Shape::stack, kSlots = 64;
-    constexpr int kStacks = TEAM > 1 ? 1 : kAdjWaves;
-    static_assert(TEAM == 1 || TEAM == kAdjWaves, "a team is a block");
+    constexpr int kWaves = block_waves(TEAM), kStacks = TEAM > 1 ? 1 : kWaves;
     struct __align__(16) Pos { R x, y, z, m; };
     struct __align__(16) Aux { R tau; uint32_t first, count; };  // opening threshold (-1: a one-particle leaf), particle range
     struct __align__(16) Tgt { R x, y, z, gx, gy, gz, h, pad; };
@@ -54,11 +53,11 @@ void k_walk_adj(WalkArgs a)
     // staged children: slot 8 j + k holds child k of group j; after the walk a team's totals
     constexpr int kTotals = 3;
     struct __align__(16) Stage { Pos pos[kSlots]; Aux aux[kSlots]; };
-    __shared__ union { Stage st[kAdjWaves]; double total[TEAM][kTotals][64]; } stage;
-    __shared__ Tgt tgt[kAdjWaves][8];          // a sparse group's targets
+    __shared__ union { Stage st[kWaves]; double total[TEAM][kTotals][64]; } stage;
+    __shared__ Tgt tgt[kWaves][8];          // a sparse group's targets
     // source-side values of two pairs of nodes: row p holds, by component, the lanes' halves of
     // the pair's first node (0-31) and of its second (32-63), each already summed over lanes l, l + 32
-    __shared__ __align__(16) R sval[kAdjWaves][2][4][64];
+    __shared__ __align__(16) R sval[kWaves][2][4][64];
     __shared__ uint32_t pushes[2][TEAM];
     R tau0;
     if constexpr (F64) tau0 = a.tau0_64;
@@ -75,7 +74,7 @@ void k_walk_adj(WalkArgs a)
     const uint32_t nb = gridDim.x, b = blockIdx.x, full = nb / (8 * kXcdRun) * (8 * kXcdRun);
     const uint32_t i8 = b >> 3;
     const uint32_t lb = b < full ? ((i8 / kXcdRun) * 8 + (b & 7u)) * kXcdRun + i8 % kXcdRun : b;
-    const int64_t wave_id = TEAM > 1 ? (int64_t)lb : (int64_t)lb * kAdjWaves + w;  // 64 targets
+    const int64_t wave_id = TEAM > 1 ? (int64_t)lb : (int64_t)lb * kWaves + w;  // 64 targets
     const int64_t base = wave_id * 64;
     if (base >= a.n) return;  // the whole wave; of a team, the whole block
     // this lane's target (sorted position) and the range of sorted positions the
@@ -479,23 +478,47 @@ void k_walk_adj(WalkArgs a)
 
 }  // namespace
 
-// Adjoint walk times in us, team / one wavefront (Plummer, theta = 0.5):
-//   F32C  65536: 337 / 879    262144: 952 / 1363    1000000: 3541 / 3735    2000000: 7079 / 6797
-//   FP64  65536: 499 / 1024   262144: 1621 / 1940   1000000: 6915 / 6237
-bool adjoint_team(int64_t n, tc_walk mode) { return n <= (mode == TC_WALK_F64 ? 3 << 17 : 1 << 20); }
+// A team of 16 fills a CU, so 16384 particles fill the chip; beyond, smaller teams
+// waste less on the tree's top, where a step has few groups to share.  Walk times
+// in us, teams of 16 / 8 / 4 (lognormal, theta = 0.5; below, 4 / one wavefront, Plummer):
+//   F32C  8192: 124 / 139 / 200    16384: 132 / 154 / 222    32768: 254 / 200 / 261    65536: 497 / 352 / 337
+//   FP64  8192: 153 / 176 / 237    16384: 170 / 195 / 261    20000: 269 / 239 / 287    32768: 328 / 277 / 341
+//         65536: 656 / 522 / 479
+//   F32C  262144: 952 / 1363    1000000: 3541 / 3735    2000000: 7079 / 6797
+//   FP64  262144: 1621 / 1940   1000000: 6915 / 6237
+int adjoint_team(int64_t n, tc_walk mode)
+{
+    if (n <= 1 << 14) return 16;
+    if (n <= 3 << 14) return 8;
+    return n <= (mode == TC_WALK_F64 ? 3 << 17 : 1 << 20) ? 4 : 1;
+}
 
-void launch_walk_adjoint_wide(const WalkArgs& a, tc_walk mode, bool team, hipStream_t s)
+namespace {
+
+template <bool F64, int TEAM>
+void launch_adj(const WalkArgs& a, hipStream_t s)
+{
+    const int64_t waves = walk_waves(a.n);
+    const unsigned blocks = (unsigned)(TEAM > 1 ? waves : (waves + kAdjWaves - 1) / kAdjWaves);
+    k_walk_adj<F64, TEAM><<<blocks, 64 * block_waves(TEAM), 0, s>>>(a);
+}
+
+template <bool F64>
+void launch_adj_team(const WalkArgs& a, int team, hipStream_t s)
+{
+    if (team == 16) launch_adj<F64, 16>(a, s);
+    else if (team == 8) launch_adj<F64, 8>(a, s);
+    else if (team == 4) launch_adj<F64, 4>(a, s);
+    else launch_adj<F64, 1>(a, s);
+}
+
+}  // namespace
+
+void launch_walk_adjoint_wide(const WalkArgs& a, tc_walk mode, int team, hipStream_t s)
 {
     if (a.n == 0) return;
-    const int64_t waves = walk_waves(a.n);
-    const unsigned blocks = (unsigned)(team ? waves : (waves + kAdjWaves - 1) / kAdjWaves);
-    if (mode == TC_WALK_F64) {
-        if (team) k_walk_adj<true, kAdjWaves><<<blocks, kAdjThreads, 0, s>>>(a);
-        else k_walk_adj<true, 1><<<blocks, kAdjThreads, 0, s>>>(a);
-    } else {
-        if (team) k_walk_adj<false, kAdjWaves><<<blocks, kAdjThreads, 0, s>>>(a);
-        else k_walk_adj<false, 1><<<blocks, kAdjThreads, 0, s>>>(a);
-    }
+    if (mode == TC_WALK_F64) launch_adj_team<true>(a, team, s);
+    else launch_adj_team<false>(a, team, s);
 }
 
 }  // namespace tc

@@ -369,10 +369,10 @@ int64_t walk_rows_max(int64_t n)
 }
 
 // The adjoint adds to a node's gradient with four atomics per wavefront and node,
-// so fewer targets a wavefront mean more atomics (us, T = 8 / 16 / team):
-//   F32C  8192: 128 / 144 / 205    16384: 242 / 238 / 227    65536: 880 / 667 / 337
-//   FP64  8192: 129 / 168 / -      16384: 225 / 271 / 263    65536: - / 743 / 499
-int adjoint_targets(int64_t n, tc_walk mode) { return n <= (mode == TC_WALK_F64 ? 1 << 14 : 3 << 12) ? 8 : 64; }
+// so fewer targets a wavefront mean more atomics (us, T = 8 / a team for 64 targets):
+//   F32C  4096: 107 / 111    8192: 151 / 124    16384: 251 / 132
+//   FP64  4096: 118 / 137    8192: 163 / 153    16384: 272 / 170
+int adjoint_targets(int64_t n) { return n <= 3 << 11 ? 8 : 64; }
 
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s)
 {

@@ -114,7 +114,8 @@ def test_wide_walk_matches_oracle(name, walk):
 
 
 @pytest.mark.parametrize("walk,n", [("f32c", 12288), ("f32c", 12289), ("f32c", 300007), ("f32c", 1048576), ("f32c", 1048577),
-                                    ("f64", 16384), ("f64", 16385), ("f64", 393216), ("f64", 393217)])
+                                    ("f64", 16384), ("f64", 16385), ("f64", 393216), ("f64", 393217)]
+                         + [(w, n) for w in ("f32c", "f64") for n in (6144, 6145, 49152, 49153)] + [("f32c", 16385), ("f64", 6151)])
 @pytest.mark.parametrize("name", ["plummer", "clumps", "dups"])
 def test_wide_adjoint_matches_replay(name, walk, n):
     """The adjoint walks against the replay of stored lists on the same
