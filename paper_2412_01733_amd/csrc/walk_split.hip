@@ -10,6 +10,11 @@
 // open fewer nodes between them).  The price is that a node record is staged for
 // T targets instead of 64, which is why large inputs stay with walk_forward.hip.
 //
+// A team: 2 or 4 wavefronts, the block, serve the same T targets, share one stack
+// and take an equal part of each step's groups each, so that the chain is shorter
+// still (the walk at 1000 particles: 46 us alone, 24 with four); once the chip is
+// full the two barriers of a step and the part-filled runs cost more than that.
+//
 // A step takes up to 8 sibling groups off the stack and stages their <= 64
 // children, one per lane.  The box test of walk_forward.hip sorts the children into
 // accepted by every target (list A, compacted in LDS), opened by every target of
@@ -29,7 +34,7 @@ namespace tc {
 namespace {
 
 constexpr int kSplitWaves = 4;
-constexpr int kSplitThreads = 64 * kSplitWaves;
+constexpr int block_waves(int team) { return team > 1 ? team : kSplitWaves; }  // a team is a block
 // Stack bound.  An entry at position p whose nodes lie at level l is safe if
 //   p + 1 + 7 + 7 (20 - l) + 1 <= kSplitStack:
 // a depth-first descent from it grows the stack by at most 7 a level.  Group j
@@ -38,6 +43,7 @@ constexpr int kSplitThreads = 64 * kSplitWaves;
 // makes its children's groups safe in turn; the top group always satisfies this,
 // by being safe, and the first entry does (142).
 constexpr int kSplitStack = 256;
+constexpr int kTeamStack = 400;
 static_assert(kSplitStack >= 142, "the root's children must be safe");
 
 // group entry: first node, mask (bits 0-15) | child count (16-19) | level of the nodes (20-24)
@@ -46,29 +52,33 @@ __device__ inline uint32_t pack_group(uint32_t mask, uint32_t nchild, uint32_t l
     return mask | (nchild << 16) | (level << 20);
 }
 
-template <bool F64, int T, bool ADJ>
-__global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
+template <bool F64, int T, bool ADJ, int TEAM>
+__global__ __launch_bounds__(64 * block_waves(TEAM)) void k_walk_split(WalkArgs a)
 {
+    constexpr int kWaves = block_waves(TEAM), kStacks = TEAM > 1 ? 1 : kWaves, kStack = TEAM > 1 ? kTeamStack : kSplitStack;
     constexpr int S = 64 / T;
     constexpr uint32_t kMaskT = (1u << T) - 1u;
     using R = typename std::conditional<F64, double, float>::type;
     struct __align__(16) Rec { R x, y, z, m; };
     constexpr int kRec = 64 + 2 * S;  // lists A and M, each padded to whole runs of S
-    __shared__ uint2 stk[kSplitWaves][kSplitStack];
-    __shared__ Rec rec[kSplitWaves][kRec];
-    __shared__ uint32_t rmask[kSplitWaves][kRec];  // targets (bits 0-15) | staging lane << 16
-    __shared__ R stau[kSplitWaves][64];            // by staging lane: opening threshold,
-    __shared__ uint2 srange[kSplitWaves][64];      // first particle and count,
-    __shared__ uint32_t somask[kSplitWaves][64];   // targets that open the child
-    __shared__ uint32_t rnode[ADJ ? kSplitWaves : 1][ADJ ? kRec : 1];
+    __shared__ uint2 stk[kStacks][kStack];
+    __shared__ Rec rec[kWaves][kRec];
+    __shared__ uint32_t rmask[kWaves][kRec];  // targets (bits 0-15) | staging lane << 16
+    __shared__ R stau[kWaves][64];            // by staging lane: opening threshold,
+    __shared__ uint2 srange[kWaves][64];      // first particle and count,
+    __shared__ uint32_t somask[kWaves][64];   // targets that open the child
+    __shared__ uint32_t pushes[2][TEAM];
+    __shared__ double total[TEAM][4][TEAM > 1 ? T : 1];
+    __shared__ uint32_t rnode[ADJ ? kWaves : 1][ADJ ? kRec : 1];
 
     const int w = (int)(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t t = lane % T, s = lane / T;
     const uint32_t tbit = 1u << t;
-    const int64_t wave_id = (int64_t)blockIdx.x * kSplitWaves + w;
+    const int sw = TEAM > 1 ? 0 : w;  // whose stack
+    const int64_t wave_id = TEAM > 1 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kWaves + w;  // T targets
     const int64_t base = wave_id * T;
-    if (base >= a.n) return;  // whole wave; no block barrier follows
+    if (base >= a.n) return;  // the whole wave; of a team, the whole block
     R tau0;
     if constexpr (F64) tau0 = a.tau0_64;
     else tau0 = a.tau0_32;
@@ -149,27 +159,43 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
     const uint32_t rmeta = uni(a.nodes[0].meta);
     if (!meta_leaf(rmeta)) {
         const uint32_t live = (uint32_t)__ballot(valid) & kMaskT;
-        if (lane == 0) stk[w][0] = make_uint2(uni(a.nodes[0].child), pack_group(live, meta_nchild(rmeta), 1u));
+        if (lane == 0 && w == sw) stk[sw][0] = make_uint2(uni(a.nodes[0].child), pack_group(live, meta_nchild(rmeta), 1u));
         sp = 1;
     }
-    wave_sync();
+    team_sync<TEAM>();
 
     const uint32_t gj = lane >> 3, gk = lane & 7;
-    int since_fold = 0;
+    int since_fold = 0, turn = 0;
     while (sp > 0) {
         // take the groups that the stack bound allows off the top; lanes 8 j .. 8 j + 7 stage group j
+        // (of a team's groups a wavefront takes up to 8, from the j0-th off the top)
         uint2 e = make_uint2(0u, 0u);
-        bool ok = false;
-        if ((int)gj < sp) {
-            e = stk[w][sp - 1 - (int)gj];
-            const int l = (int)((e.y >> 20) & 31u);
-            ok = gj == 0 || sp + 7 * ((int)gj + 1) + 7 * (20 - l) + 1 <= kSplitStack;
+        int ng, mine;
+        if constexpr (TEAM == 1) {
+            bool ok = false;
+            if ((int)gj < sp) {
+                e = stk[sw][sp - 1 - (int)gj];
+                const int l = (int)((e.y >> 20) & 31u);
+                ok = gj == 0 || sp + 7 * ((int)gj + 1) + 7 * (20 - l) + 1 <= kStack;
+            }
+            const uint64_t okm = __ballot(ok);
+            ng = ~okm ? (int)(__builtin_ctzll(~okm) >> 3) : 8;
+            mine = ng;
+        } else {
+            bool ok = false;
+            if ((int)lane < min(sp, 8 * TEAM)) {
+                const int l = (int)((stk[0][sp - 1 - (int)lane].y >> 20) & 31u);
+                ok = lane == 0 || sp + 7 * ((int)lane + 1) + 7 * (20 - l) + 1 <= kStack;
+            }
+            const uint64_t okm = __ballot(ok);
+            ng = uni(~okm ? (int)__builtin_ctzll(~okm) : 64);
+            const int q = (ng + TEAM - 1) / TEAM, j0 = w * q;
+            mine = max(0, min(q, ng - j0));
+            if ((int)gj < mine) e = stk[0][sp - 1 - j0 - (int)gj];
         }
-        const uint64_t okm = __ballot(ok);
-        const int ng = ~okm ? (int)(__builtin_ctzll(~okm) >> 3) : 8;
         sp = uni(sp - ng);
         const uint32_t nc = (e.y >> 16) & 15u, pmask = e.y & 0xFFFFu;
-        const bool live = (int)gj < ng && gk < min(nc, 8u);
+        const bool live = (int)gj < mine && gk < min(nc, 8u);
         if (__ballot(live && nc > 8u)) corrupt = true;
         bool far_all = false, near_all = false;
         uint32_t child = 0, meta = 0, first = 0, count = 0;
@@ -252,13 +278,26 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
         const bool leaf = meta_leaf(meta);
         const uint64_t pm = __ballot(open != 0u && !leaf);
         const int np = (int)__popcll(pm);
-        if (sp + np > kSplitStack) {
+        int before = 0, all = np;
+        if constexpr (TEAM > 1) {
+            // the waves' pushes follow each other in the order of their groups
+            if (lane == 0) pushes[turn][w] = (uint32_t)np;
+            __syncthreads();  // also: every wave has read its groups
+            all = 0;
+            for (int u = 0; u < TEAM; ++u) {
+                const int c = (int)pushes[turn][u];
+                if (u < w) before += c;
+                all += c;
+            }
+            turn ^= 1;
+        }
+        if (sp + all > kStack) {
             stack_over = true;  // cannot happen (see the bound); refused and flagged
         } else {
             if (open != 0u && !leaf)
-                stk[w][sp + (int)popc_below(pm)] =
+                stk[sw][sp + before + (int)popc_below(pm)] =
                     make_uint2(child, pack_group(open, meta_nchild(meta), meta_level(meta) + 1u));
-            sp = uni(sp + np);
+            sp = uni(sp + all);
         }
         for (uint64_t lm = __ballot(open != 0u && leaf && count > 1u); lm; lm &= lm - 1ull) {
             const int src = (int)__builtin_ctzll(lm);
@@ -300,7 +339,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
                 }
             }
         }
-        wave_sync();
+        team_sync<TEAM>();
         // at most 64 / S terms a lane and step go into the plain sums
         if (++since_fold == 2 || sp == 0) {
             since_fold = 0;
@@ -329,6 +368,20 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
     for (int o = T; o < 64; o <<= 1)
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] += __shfl_xor(v[k], o, 64);
+    if constexpr (TEAM > 1) {
+        // the waves' totals, added in the waves' order
+        if (s == 0)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) total[w][k][t] = v[k];
+        __syncthreads();
+        if (w > 0) return;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = total[0][k][t];
+#pragma unroll
+        for (int u = 1; u < TEAM; ++u)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] += total[u][k][t];
+    }
 
     if constexpr (ADJ) {
         if (valid && s == 0) {
@@ -340,25 +393,37 @@ __global__ __launch_bounds__(kSplitThreads) void k_walk_split(WalkArgs a)
     }
 }
 
-template <int T, bool ADJ>
-void launch_split(const WalkArgs& a, tc_walk mode, hipStream_t s)
+template <bool F64, int T, bool ADJ, int TEAM>
+void launch_split(const WalkArgs& a, hipStream_t s)
 {
     const int64_t waves = (a.n + T - 1) / T;
-    const unsigned blocks = (unsigned)((waves + kSplitWaves - 1) / kSplitWaves);
-    if (mode == TC_WALK_F64) k_walk_split<true, T, ADJ><<<blocks, kSplitThreads, 0, s>>>(a);
-    else k_walk_split<false, T, ADJ><<<blocks, kSplitThreads, 0, s>>>(a);
+    const unsigned blocks = (unsigned)(TEAM > 1 ? waves : (waves + kSplitWaves - 1) / kSplitWaves);
+    k_walk_split<F64, T, ADJ, TEAM><<<blocks, 64 * block_waves(TEAM), 0, s>>>(a);
 }
 
 }  // namespace
 
-// Where the lines lie (walk times in us on one MI355X, Plummer, theta = 0.5; T = 8 /
-// T = 16 / a team of four wavefronts for 64 targets, see walk_forward.hip):
-//   F32C  32768: 95 / 118 / 145    49152: 143 / 135 / -    65536: 169 / 155 / 185
-//         131072: 300 / 262 / 246  262144: 575 / 469 / 411
-//   FP64  65536: 225 / 216 / 231   262144: 845 / 718 / 656
+// Where the lines lie (walk times in us on one MI355X, Plummer, theta = 0.5; T targets /
+// wavefronts that share them; 64 / 4: the team of walk_forward.hip):
+//             8/1   8/2   8/4   8/8   16/1  16/2  16/4  64/4
+//   F32C 1000   46    32    24    24    60    40    28     -
+//        4096   62    43    31    33    95    62    40   106
+//        8192   69    48    36    55   102    67    43     -
+//       16384   77    56    63    93   113    73    52   132
+//       32768   92   100   111   170   116    85    89   143
+//       65536  171   180   213   342   155   151   159   180
+//       98000  235   256   313   504   218   210   225     -
+//      131072  300     -     -     -   262     -     -   244
+//   FP64 4096   65    44    33    36    99    65    42   128
+//        8192   73    51    42    66   108    72    47     -
+//       16384   87    69    80   125   120    83    67   154
+//       32768  123   131   146   242   139   117   120   180
+//       65536  228   246   288   491   220   214   224   238
+//      100000  336   366   435   758   306   317   338   318
+//      131072  431   479   571   994   378   403   437   406
 int walk_targets(int64_t n, tc_walk mode)
 {
-    if (n <= 5 << 13) return 8;
+    if (n <= 3 << 12) return 8;
     return n <= (mode == TC_WALK_F64 ? 1 << 17 : 3 << 15) ? 16 : 64;
 }
 
@@ -369,22 +434,27 @@ int64_t walk_rows_max(int64_t n)
 }
 
 // The adjoint adds to a node's gradient with four atomics per wavefront and node,
-// so fewer targets a wavefront mean more atomics (us, T = 8 / a team for 64 targets):
-//   F32C  4096: 107 / 111    8192: 151 / 124    16384: 251 / 132
-//   FP64  4096: 118 / 137    8192: 163 / 153    16384: 272 / 170
-int adjoint_targets(int64_t n) { return n <= 3 << 11 ? 8 : 64; }
+// so fewer targets a wavefront mean more atomics (us; T = 8 with 1 / 2 / 4 / 8
+// wavefronts, and 16 wavefronts for 64 targets, see walk_adjoint.hip):
+//   F32C  1000: 68 / 47 / 36 / 33, -    4096: 107 / 80 / 63 / 66, 111    8192: 159 / 132 / 131 / 118, 124
+//   FP64  1000: 75 / 50 / 38 / 36, -    4096: 122 / 85 / 70 / 67, 137    8192: 170 / 144 / 131 / 125, 153
+int adjoint_targets(int64_t n) { return n <= 7 << 10 ? 8 : 64; }
 
 void launch_walk_split(const WalkArgs& a, int targets, tc_walk mode, hipStream_t s)
 {
     if (a.n == 0) return;
-    if (targets == 8) launch_split<8, false>(a, mode, s);
-    else launch_split<16, false>(a, mode, s);
+    const bool f64 = mode == TC_WALK_F64;
+    if (targets == 8) f64 ? launch_split<true, 8, false, 4>(a, s) : launch_split<false, 8, false, 4>(a, s);
+    else if (a.n <= 3 << 13) f64 ? launch_split<true, 16, false, 4>(a, s) : launch_split<false, 16, false, 4>(a, s);
+    else if (!f64 || a.n <= 5 << 14) f64 ? launch_split<true, 16, false, 2>(a, s) : launch_split<false, 16, false, 2>(a, s);
+    else launch_split<true, 16, false, 1>(a, s);
 }
 
 void launch_walk_split_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s)
 {
     if (a.n == 0) return;
-    launch_split<8, true>(a, mode, s);
+    if (mode == TC_WALK_F64) launch_split<true, 8, true, 4>(a, s);
+    else launch_split<false, 8, true, 4>(a, s);
 }
 
 }  // namespace tc

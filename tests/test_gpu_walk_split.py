@@ -23,7 +23,7 @@ def _dups(n, seed):
     return pos, np.full(n, 1.0 / n)
 
 
-CASES = [("n%d" % n, lambda n=n: workloads.plummer(n, 500 + n), 0.6, 0.05) for n in (2, 7, 8, 9, 17, 63, 65, 1001)]
+CASES = [("n%d" % n, lambda n=n: workloads.plummer(n, 500 + n), 0.6, 0.05) for n in (2, 7, 8, 9, 17, 63, 65, 1001, 12301)]
 CASES += [
     ("dups4097", lambda: _dups(4097, 4), 0.6, 0.001),
     ("direct3001", lambda: workloads.plummer(3001, 77), 0.0, 0.01),
@@ -64,7 +64,8 @@ def test_split_walks_match_oracle(name, make, theta, eps, walk):
     assert abs(st["sum_m_abs_a"] / (md * np.linalg.norm(ra, axis=1)).sum() - 1) < 1e-6
 
 
-@pytest.mark.parametrize("walk,n", [("f32c", 40960), ("f32c", 40961), ("f32c", 98304), ("f32c", 98305), ("f32c", 524288),
+@pytest.mark.parametrize("walk,n", [(w, n) for w in ("f32c", "f64") for n in (12288, 12289, 24576, 24577, 81920, 81921)] + [
+                                    ("f32c", 40960), ("f32c", 40961), ("f32c", 98304), ("f32c", 98305), ("f32c", 524288),
                                     ("f32c", 524289), ("f64", 40961), ("f64", 131072), ("f64", 131073), ("f64", 786432),
                                     ("f64", 786433)])
 def test_both_sides_of_the_lines(walk, n):
@@ -115,7 +116,7 @@ def test_wide_walk_matches_oracle(name, walk):
 
 @pytest.mark.parametrize("walk,n", [("f32c", 12288), ("f32c", 12289), ("f32c", 300007), ("f32c", 1048576), ("f32c", 1048577),
                                     ("f64", 16384), ("f64", 16385), ("f64", 393216), ("f64", 393217)]
-                         + [(w, n) for w in ("f32c", "f64") for n in (6144, 6145, 49152, 49153)] + [("f32c", 16385), ("f64", 6151)])
+                         + [(w, n) for w in ("f32c", "f64") for n in (6144, 6145, 7168, 7169, 49152, 49153)] + [("f32c", 16385), ("f64", 6151)])
 @pytest.mark.parametrize("name", ["plummer", "clumps", "dups"])
 def test_wide_adjoint_matches_replay(name, walk, n):
     """The adjoint walks against the replay of stored lists on the same
