@@ -7,7 +7,7 @@
 // loaded coalesced, one particle a lane, its offsets from the block's anchor are
 // formed in FP64, and the 64 records are read back from LDS by all lanes.  Bound
 // by the 14 vector instructions of a term; the split over 16 wavefronts fills
-// the chip from ~4000 particles on (12345 particles: walk 996 -> 96 us, 1.6e12 terms a second; 1e5: 3.9 ms).
+// the chip from ~4000 particles on (12345 particles: walk 996 -> 104 us, 1.5e12 terms a second).
 //
 // Precision as in walk_forward.hip: the FP32 offsets are those the walk would
 // use (same anchor), the sums Kahan-compensated.  Particles that share a level-21
@@ -20,6 +20,9 @@ namespace tc {
 namespace {
 
 constexpr int kDirectWaves = 16;
+// Terms of a plain partial sum (F32C potentials against FP64 at 5000 particles:
+// 2.95e-8 with 64, 2.63e-8 with 32, as the walk (2.57e-8) with 16).
+constexpr int kFold = 16;
 
 template <bool F64>
 __global__ __launch_bounds__(64 * kDirectWaves) void k_direct(WalkArgs a)
@@ -79,32 +82,40 @@ __global__ __launch_bounds__(64 * kDirectWaves) void k_direct(WalkArgs a)
             src[w][lane] = h;
         }
         wave_sync();
+        auto fold = [&]() {
+            if constexpr (F64) {
+                tx += bx; ty += by; tz += bz; tp += bp;
+            } else {
+                kahan_add(tx, cx, bx);
+                kahan_add(ty, cy, by);
+                kahan_add(tz, cz, bz);
+                kahan_add(tp, cp, bp);
+            }
+            bx = 0; by = 0; bz = 0; bp = 0;
+        };
+        int k = 0;
         if (j0 + cnt <= own_lo || j0 >= own_end) {
-            int k = 0;
-            for (; k + 8 <= cnt; k += 8) {
-                Pos h[8];
+            for (; k + kFold <= cnt; k += kFold) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) h[u] = src[w][k + u];
+                for (int v = 0; v < kFold; v += 8) {
+                    Pos h[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) term(h[u]);
+                    for (int u = 0; u < 8; ++u) h[u] = src[w][k + v + u];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) term(h[u]);
+                }
+                fold();
             }
             for (; k < cnt; ++k) term(src[w][k]);
         } else {  // may hold a target: itself excluded
-            for (int k = 0; k < cnt; ++k) {
+            for (; k < cnt; ++k) {
                 const Pos h = src[w][k];
                 if ((uint32_t)(j0 + k) != su) term(h);
+                if (k % kFold == kFold - 1) fold();
             }
         }
+        fold();
         wave_sync();
-        if constexpr (F64) {
-            tx += bx; ty += by; tz += bz; tp += bp;
-        } else {
-            kahan_add(tx, cx, bx);
-            kahan_add(ty, cy, by);
-            kahan_add(tz, cz, bz);
-            kahan_add(tp, cp, bp);
-        }
-        bx = 0; by = 0; bz = 0; bp = 0;
     }
     total[w][0][lane] = F64 ? (double)tx : (double)tx - (double)cx;
     total[w][1][lane] = F64 ? (double)ty : (double)ty - (double)cy;
