@@ -37,7 +37,7 @@ FLOPS_PER_INTERACTION = 20          # acc + pot, rsqrt counted as one
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "walk_f32c_plummer1e7_traffic.txt")
 WALK_SRC = os.path.join(ROOT, "paper_2412_01733_amd", "csrc", "walk_forward.hip")
 BUILD_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "build_plummer1e7_traffic.md")
-BUILD_SRCS = ["keys.hip", "sort.hip", "scan.hip", "build.hip", "moments.hip", "order.hip"]
+BUILD_SRCS = ["keys.hip", "sort.hip", "scan.hip", "sort_small.hip", "build.hip", "moments.hip", "order.hip"]
 PEAK_FP32_TFLOPS = 157.3             # MI355X FP32 vector (packed FMA)
 PEAK_FP32_NONPACKED_TFLOPS = 78.6    # one FMA per lane per clock: 256 CU x 64 lanes x 2 x 2.4 GHz
 PEAK_FP64_TFLOPS = 78.6
@@ -102,13 +102,14 @@ def stage_bytes(n, nn, p=4):
     """Compulsory HBM bytes of each build stage: what its kernels read and
     write once (no re-reads), for n particles, nn nodes and p-byte inputs."""
     keys = n * (4 * p + (4 * p + 8 + 4 + 4 * p))            # bounds; keys + index + packed record
-    sort = n * (8 * (8 + 24) + (4 + 4 * p + 32))             # 8 radix passes (count + move); gather
-    tree = n * (9 + 5 + 8 + 13) + nn * (14 + 13 + 13 + 32 + 8)  # adjacent, counts, scan, emit; node passes
-    # leaf particles; per node: index, pre-order fields and octant, first child, children's moments, record,
-    # parent link, dense topology record; then the target order: per node its topology record (read by
-    # itself and by its parent) and its {offset, Hilbert state} (written by the parent, read by itself),
-    # per particle its place
-    moments = n * 32 + nn * (4 + 13 + 4 + 32 + 48 + 4 + 16) + nn * (16 + 16 + 8 + 8) + n * 4
+    sort = n * (7 * (8 + 24) + (4 + 4 * p + 32))             # 7 radix passes (count + move); gather
+    inner = nn - n                                           # nodes of several particles
+    # counts: keys; emit: keys and particles, leaf numbers and one-particle records, links
+    tree = n * (8 + 8 + 32 + 4 + 48) + nn * 16 + inner * 8
+    # per node: its links, its record as a child; per inner node: ends, record.  Then the target order:
+    # per node its links (read by itself and by its parent) and {distance, parent}, per inner node its
+    # key and ends (read by itself and by its parent), per particle its leaf, a step up and its place
+    moments = nn * (16 + 32) + inner * (8 + 48) + nn * (16 + 16 + 8) + inner * (8 + 8 + 8) + n * (4 + 16 + 8 + 4)
     return dict(keys=keys, sort=sort, tree=tree, moments=moments)
 
 
@@ -433,7 +434,7 @@ def main():
                    "theta": args.theta, "eps": args.eps, "walk": head, "inputs": "fp32, seed %d" % args.seed},
         "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": walk_traffic_bytes() if head == "f32c" else None,
-                     "kernel": "k_walk<%s>" % ("F32C" if head == "f32c" else "F64"),
+                     "kernel": "k_walk_fwd<%s>" % ("F32C" if head == "f32c" else "F64"),
                      "flops_per_interaction": FLOPS_PER_INTERACTION, "interactions": r["interactions"],
                      "walk_ms": r["walk_ms"],
                      "frac_nonpacked_fp32": (achieved / PEAK_FP32_NONPACKED_TFLOPS) if head == "f32c" else None},

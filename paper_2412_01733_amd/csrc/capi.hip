@@ -338,8 +338,8 @@ tc_status mark_done(tc_tree* t, hipStream_t s, tc_status st)
 // Status word of the walks, cleared by each build and kept until the next
 // (bit 0: a traversal stack would have overflowed, so terms were dropped;
 // bit 1: a node with more than 8 children, i.e. a corrupt tree).  Neither can
-// happen for a tree built by tc_build (the stack bound is proven in
-// walk.hip); both are checked wherever the host synchronises anyway.
+// happen for a tree built by tc_build (each walk's file proves its stack
+// bound); both are checked wherever the host synchronises anyway.
 tc_status walk_status_error(tc_tree* t)
 {
     if (!t->walk_status_pending) return TC_OK;

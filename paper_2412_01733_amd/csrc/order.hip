@@ -1,10 +1,10 @@
 // The walk's target order: the particles along the Hilbert curve.
 //
-// The walk gives each wavefront 64 consecutive targets of this order.  The
+// The walk gives each wavefront 8, 16 or 64 consecutive targets of this order.  The
 // tree, its keys and its node table stay in Morton (key) order; only the
 // grouping of targets into wavefronts changes.  A Hilbert segment of 64
 // particles is spatially more compact than a Morton segment, which jumps
-// between distant cells at the Z-curve's seams, so the 64 lanes open fewer
+// between distant cells at the Z-curve's seams, so the targets open fewer
 // nodes between them.  No result depends on the order: every target's
 // interaction set and terms are its own.
 //

@@ -1,4 +1,5 @@
-// The storing walk (TC_STORE_LISTS) and the adjoint walk (tc_forces_backward).
+// The storing walk (TC_STORE_LISTS) and the adjoint that replays its lists
+// (tc_forces_backward; without lists it is walk_adjoint.hip or walk_split.hip).
 //
 // Both walk the tree for 64 consecutive targets of the target order a wavefront,
 // with the decisions of walk_forward.hip bit for bit (same anchor, same

@@ -1,4 +1,4 @@
-// Device helpers shared by the walk kernels (walk.hip, walk_split.hip).
+// Device helpers shared by the walk kernels.
 #pragma once
 
 #include "tc_internal.h"

@@ -40,7 +40,7 @@
 // per-wave FP64 anchor (the first target of the wave), formed in FP64 once
 // per staged node, so differences stay small and accurate; interactions are
 // FP32 (hardware reciprocal square root); plain partial sums are added every
-// second step into per-lane Kahan-compensated totals.  F64: absolute FP64
+// step into per-lane Kahan-compensated totals.  F64: absolute FP64
 // coordinates, FP64 reciprocal square root refined by one third-order
 // correction, plain FP64 sums.  Both walks also reduce sum_i m_i a_i and
 // sum_i m_i |a_i| in FP64, one partial per wave, for the momentum diagnostic.
