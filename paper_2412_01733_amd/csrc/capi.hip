@@ -569,16 +569,22 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     stage_begin(t, kStBwdWalk, s);
     launch_fill_f64_zero(a.node_grad, nn * 4, s);
     if (multi) launch_fill_f64_zero(a.part_grad, n * 4, s);
-    const int targets = t->lists_stored ? 64 : adjoint_targets(n);
+    // FP32 sums handed back as the gradients of FP64 particles keep the order and the
+    // partial sums of the single-group walk (walk.hip, which also replays lists).
+    // Another order moves them by the FP32 rounding, 1e-7, which is much for an FP64
+    // result; the faster walks are for gradients of the walk's own precision (at 21708
+    // particles, theta = 0.3, a pass takes 3.1 ms with this walk, 0.8 ms with those).
+    const bool single_groups = t->lists_stored || (t->dtype == TC_F64 && t->last_mode == TC_WALK_F32C);
+    const int targets = single_groups ? 64 : adjoint_targets(n);
     if (targets < 64) launch_walk_split_adjoint(a, t->last_mode, s);
-    else if (t->lists_stored) launch_walk_adjoint(a, t->last_mode, s);
+    else if (single_groups) launch_walk_adjoint(a, t->last_mode, s);
     else launch_walk_adjoint_wide(a, t->last_mode, adjoint_team(n, t->last_mode), s);
     stage_end(t, kStBwdWalk, s);
     TC_TRY(check_launch("adjoint walk"));
     HIP_TRY(hipMemcpyAsync(&t->host->status, t->status, 4, hipMemcpyDeviceToHost, s));
     t->walk_status_pending = true;
     stage_begin(t, kStBwdDown, s);
-    launch_adjoint_down(t->host->level_off, n, P<uint4>(t->topo), P<WalkNode>(t->wn), P<uint2>(t->up), a.node_grad,
+    launch_adjoint_down(nn, n, P<uint4>(t->topo), P<WalkNode>(t->wn), P<uint2>(t->up), a.node_grad,
                         P<double>(t->uc), P<uint32_t>(t->leaf_of), a.sp, t->perm, a.target_grad, a.part_grad, g_pos, g_mass,
                         t->last_mode == TC_WALK_F64, s);
     stage_end(t, kStBwdDown, s);

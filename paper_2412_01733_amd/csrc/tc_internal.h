@@ -192,8 +192,8 @@ void launch_walk_split_adjoint(const WalkArgs& a, tc_walk mode, hipStream_t s);
 void launch_target_order(int64_t n, int64_t nn, const uint64_t* skeys, const uint4* topo, const uint2* ends,
                          const uint32_t* leaf_of, uint2* up, uint32_t* order, hipStream_t s);
 
-// adjoint.hip: top-down pass from node gradients to particle gradients.
-void launch_adjoint_down(const uint32_t* level_off_host, int64_t n, const uint4* topo, const WalkNode* wn, const uint2* up,
+// adjoint.hip: from node gradients to particle gradients.
+void launch_adjoint_down(int64_t nn, int64_t n, const uint4* topo, const WalkNode* wn, const uint2* up,
                          const double* node_grad, double* uc, const uint32_t* leaf_of, const Particle* sp,
                          const uint32_t* perm, const double* target_grad, const double* part_grad, void* g_pos,
                          void* g_mass, bool out_f64, hipStream_t s);

@@ -73,14 +73,14 @@ __device__ inline void adj_term(R dx, R dy, R dz, R q, R mu, R gx, R gy, R gz, R
 {
     const R ri = rsqrt_any(q);
     const R ri2 = ri * ri;
+    const R ri3 = ri2 * ri;
     const R dg = fma(dx, gx, fma(dy, gy, dz * gz));
-    const R e = dg * ri2, w = fma(-dg, ri2, h);
-    const R c1 = mu * ri * ri2;
-    const R c2 = c1 * fma((R)-2, e, w);  // mu q^-3/2 (h - 3 Delta.g / q)
+    const R c1 = mu * ri3;
+    const R c2 = c1 * fma((R)-3 * ri2, dg, h);
     sx = fma(c1, gx, c2 * dx);
     sy = fma(c1, gy, c2 * dy);
     sz = fma(c1, gz, c2 * dz);
-    sm = -ri * w;
+    sm = fma(dg, ri3, -h * ri);
 }
 
 // Sum over the wave of four values; the result is uniform.

@@ -175,3 +175,46 @@ def test_direct_sum_with_shared_cells_takes_the_walk(walk):
     ra, rp = oracle.direct(pos, m, 0.001)
     check_errors(rel_err(acc.cpu().numpy(), ra), walk, what="acc")
     check_errors(rel_err(pot.cpu().numpy(), rp), walk, what="pot")
+
+
+@pytest.mark.parametrize("walk", ["f32c", "f64"])
+@pytest.mark.parametrize("name", ["one", "coincident", "pair", "chain"])
+def test_climb_to_the_root(name, walk):
+    """Gradients where the way from a particle's leaf to the root has no step (the
+    root is the leaf), one, or all 21 (particles 2^-20 of the cube apart)."""
+    import paper_2412_01733_amd as tc
+    pos = {"one": [[0.5, 0.25, 0.125]], "coincident": [[0.5, 0.25, 0.125]] * 5, "pair": [[0.0, 0.0, 0.0], [1.0, 0.5, 0.25]],
+           "chain": [[0.0, 0.0, 0.0], [2.0 ** -20, 0.0, 0.0], [0.0, 2.0 ** -21, 0.0], [1.0, 1.0, 1.0]]}[name]
+    pos = np.array(pos)
+    n = len(pos)
+    m = np.arange(1.0, n + 1) / n
+    p, mm = _gpu(pos, m)
+    _, _, tree = tc.forces(p, mm, 0.7, 0.5, walk=walk)
+    g = np.random.default_rng(3)
+    ga, gp = g.standard_normal((n, 3)), g.standard_normal(n)
+    gx, gm = tree.backward(torch.from_numpy(ga).to(p.device), torch.from_numpy(gp).to(p.device))
+    T = oracle.Tree(pos, m)
+    ox, om = T.frozen_adjoint(T.lists(0.7), 0.5, ga, gp)
+    # a few terms of order |g| m / eps^3 = O(10), each within a few roundings
+    tol = 1e-5 if walk == "f32c" else 1e-13
+    assert np.abs(gx.cpu().numpy() - ox).max() <= 10 * tol and np.abs(gm.cpu().numpy() - om).max() <= 10 * tol
+
+
+@pytest.mark.parametrize("n", [9001, 16385])
+def test_gradients_of_fp64_particles_are_those_of_the_single_group_walk(n):
+    """FP32 terms, FP64 particles: the walk that lists of more than 8192 records a
+    wavefront (theta = 0) fall back to, so the same sums with that flag as without
+    (only the order of the FP64 atomics differs, which flips few FP32 roundings)."""
+    import paper_2412_01733_amd as tc
+    pos, m = workloads.plummer(n, 5, mass=workloads.lognormal_masses(n, 6))
+    p, mm = _gpu(pos, m)
+    assert p.dtype == torch.float64
+    g = np.random.default_rng(n)
+    ga, gp = (torch.from_numpy(g.standard_normal(s)).to(p.device) for s in ((n, 3), n))
+    _, _, tree = tc.forces(p, mm, 0.0, 0.01, store_lists=True)
+    assert tree.stats()["lists_stored"]
+    rx, rm = tree.backward(ga, gp)
+    tree.forces(0.0, 0.01)
+    gx, gm = tree.backward(ga, gp)
+    for a, b in ((gx, rx), (gm, rm)):
+        assert (a.double() - b.double()).norm() <= 1e-8 * b.double().norm()
