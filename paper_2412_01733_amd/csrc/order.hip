@@ -128,20 +128,26 @@ __global__ __launch_bounds__(256) void k_order_children(int64_t nn, const uint64
     for (int l = 1; l <= (int)meta_level(rec.z); ++l)
         st = step[8 * st + ((uint32_t)(key >> (3 * (kMaxLevel - l))) & 7u)];
     const uint32_t dg = digits[st];
-    const uint32_t last = ends[b].y, nc = last - rec.y + 1u < 8u ? last - rec.y + 1u : 8u;
+    const uint2 en = ends[b];  // end, last child
+    const uint32_t nc = en.y - rec.y + 1u < 8u ? en.y - rec.y + 1u : 8u;
     // fixed-size, fully unrolled, so that the arrays stay in registers; an
-    // absent child counts 0 and sorts last (digit 8)
-    uint32_t cnt[8], dig[8];
+    // absent child counts 0 and sorts last (digit 8).  Siblings follow each other, so a
+    // child ends where the next begins (with the children's own ends read, 260 instead
+    // of 217 us at 1e7).
+    uint32_t first[9], cnt[8], dig[8];
+    first[8] = en.x;
 #pragma unroll
-    for (uint32_t k = 0; k < 8; ++k) {
-        cnt[k] = 0u;
+    for (int k = 7; k >= 0; --k) {
+        first[k] = en.x;
         dig[k] = 8u;
-        if (k < nc) {
-            const uint4 c = topo[rec.y + k];
-            cnt[k] = meta_single(c.z) ? 1u : ends[rec.y + k].x - c.x;
+        if ((uint32_t)k < nc) {
+            const uint4 c = topo[rec.y + (uint32_t)k];
+            first[k] = c.x;
             dig[k] = (dg >> (4 * meta_octant(c.z))) & 7u;
         }
     }
+#pragma unroll
+    for (uint32_t k = 0; k < 8; ++k) cnt[k] = first[k + 1] - first[k];
 #pragma unroll
     for (uint32_t k = 0; k < 8; ++k) {
         if (k < nc) {
