@@ -43,7 +43,8 @@ __device__ inline double4 node_mass_point(const WalkNode* __restrict__ wn, int64
     return make_double4(xy.x, xy.y, zm.x, zm.y);
 }
 
-// s += v, the rounding error of it added to e (Knuth's two-sum).
+// s += v, the rounding error of it added to e (Knuth's two-sum).  Once an infinity or an
+// overflow is met, s is the plain sum still, but e is not a number.
 __device__ inline void two_sum(double& s, double& e, double v)
 {
     const double t = s + v, b = t - s;
@@ -106,7 +107,8 @@ __global__ __launch_bounds__(256) void k_adjoint_particles(int64_t n, const uint
         two_sum(o[2], lost[2], a1.x);
         two_sum(o[3], lost[3], a1.y);
     }
-    for (int k = 0; k < 4; ++k) o[k] += lost[k];
+    for (int k = 0; k < 4; ++k)
+        if (isfinite(lost[k])) o[k] += lost[k];
     if (g_pos) {
         g_pos[3 * i + 0] = (R)(tg[0] + p0.x + q.m * o[0]);
         g_pos[3 * i + 1] = (R)(tg[1] + p0.y + q.m * o[1]);
