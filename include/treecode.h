@@ -259,8 +259,9 @@ tc_status tc_tree_target_order(const tc_tree* tree, uint32_t* order, void* strea
 tc_status tc_interaction_counts(const tc_tree* tree, uint32_t* counts, void* stream);
 
 /* Release a handle and everything it owns (NULL is a no-op).  Waits for the
- * work the handle's calls enqueued (an event recorded by each call), not for
- * the whole device, then frees. */
+ * work the handle's calls enqueued, on every stream it was used on (an event
+ * recorded by each call), not for the whole device, then frees.  Only a handle
+ * that was used on more than 4 streams waits for its device. */
 void tc_tree_free(tc_tree* tree);
 
 /* Message of the last error on this thread ("" if none). */

@@ -10,6 +10,7 @@
 #include <initializer_list>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "tc_internal.h"
@@ -69,6 +70,15 @@ struct HostMirror {
 static_assert(offsetof(HostMirror, level_hist) == sizeof(Geom) && offsetof(HostMirror, status) == offsetof(HostMirror, diag) + 32,
               "read back together");
 
+// An event recorded after the last work that a handle's calls enqueued on one stream.
+struct Mark {
+    hipEvent_t ev = nullptr;
+    hipStream_t stream = nullptr;
+    std::thread::id thread;  // hipStreamPerThread is another stream in every thread
+    bool used = false;
+};
+constexpr int kMarks = 4;  // streams a handle tells apart; beyond, tc_tree_free waits for the device
+
 }  // namespace
 
 struct tc_tree {
@@ -121,8 +131,8 @@ struct tc_tree {
     bool timing = false;
     hipEvent_t ev[2 * kNumStages] = {};
     bool ev_used[kNumStages] = {};
-    hipEvent_t done = nullptr;  // recorded after the last work each call enqueues (tc_tree_free waits on it)
-    bool unmarked = false;      // some call's completion could not be recorded: tc_tree_free waits for the device
+    Mark marks[kMarks];     // tc_tree_free waits on those used; the first has its event from the start
+    bool unmarked = false;  // some call's completion could not be recorded: tc_tree_free waits for the device
     bool walk_status_pending = false;  // a walk's status word is on its way to host->status
 };
 
@@ -246,8 +256,8 @@ tc_status carve_small(tc_tree* t, hipStream_t s)
 
 // Pinned host mirrors and completion events of freed handles, kept for the next
 // handle on the same device (a differentiable call makes and frees one each time;
-// pinning and unpinning cost 40 us).  A handle returns its pair only once its
-// enqueued work is done.  At most kHostPool of them (1.5 KiB each) are kept.
+// pinning and unpinning cost 40 us).  A handle returns its pair only once all its
+// work is known to be done.  At most kHostPool of them (1.5 KiB each) are kept.
 struct HostPair {
     int device;
     HostMirror* host;
@@ -281,6 +291,12 @@ tc_status take_host_pair(int dev, HostPair* out)
     return TC_OK;
 }
 
+void free_host_pair(const HostPair& p)
+{
+    (void)hipEventDestroy(p.done);
+    (void)hipHostFree(p.host);
+}
+
 void give_host_pair(const HostPair& p)
 {
     {
@@ -290,8 +306,7 @@ void give_host_pair(const HostPair& p)
             return;
         }
     }
-    (void)hipEventDestroy(p.done);
-    (void)hipHostFree(p.host);
+    free_host_pair(p);
 }
 
 tc_status create_tree(tc_tree** out, hipStream_t s)
@@ -319,20 +334,55 @@ tc_status create_tree(tc_tree** out, hipStream_t s)
         return st;
     }
     t->host = hp.host;
-    t->done = hp.done;
+    t->marks[0].ev = hp.done;
     memset((void*)t->host, 0, sizeof(HostMirror));
     *out = t;
     return TC_OK;
 }
 
-// Record the handle's completion event after the work a call enqueued on s.
+// Record the completion of the work a call enqueued on s.  Every stream has its own
+// event: an event says nothing about a stream it was recorded on before, and making
+// one stream wait for another is the caller's to decide.
 tc_status mark_done(tc_tree* t, hipStream_t s, tc_status st)
 {
-    if (t && t->done && hipEventRecord(t->done, s) != hipSuccess) {
+    if (!t) return st;
+    const std::thread::id me = std::this_thread::get_id();
+    Mark* m = nullptr;
+    for (Mark& q : t->marks) {
+        if (!q.used || (q.stream == s && (s != hipStreamPerThread || q.thread == me))) {
+            m = &q;
+            break;
+        }
+    }
+    if (!m || (!m->ev && hipEventCreateWithFlags(&m->ev, hipEventDisableTiming) != hipSuccess) ||
+        hipEventRecord(m->ev, s) != hipSuccess) {
         (void)hipGetLastError();
         t->unmarked = true;
+        return st;
     }
+    m->stream = s;
+    m->thread = me;
+    m->used = true;
     return st;
+}
+
+// Wait for the work the handle's calls enqueued, on whichever streams.  False if it
+// cannot be told whether all of it is done.
+bool wait_done(tc_tree* t)
+{
+    for (Mark& m : t->marks) {
+        if (m.used && hipEventSynchronize(m.ev) != hipSuccess) {
+            (void)hipGetLastError();
+            t->unmarked = true;
+        }
+    }
+    if (!t->unmarked) return true;
+    int dev = t->device;
+    bool ok = hipGetDevice(&dev) == hipSuccess && (dev == t->device || hipSetDevice(t->device) == hipSuccess);
+    ok = hipDeviceSynchronize() == hipSuccess && ok;
+    if (dev != t->device) ok = hipSetDevice(dev) == hipSuccess && ok;
+    if (!ok) (void)hipGetLastError();
+    return ok;
 }
 
 // Status word of the walks, cleared by each build and kept until the next
@@ -956,18 +1006,20 @@ tc_status tc_interaction_counts(const tc_tree* t, uint32_t* counts, void* stream
 void tc_tree_free(tc_tree* t)
 {
     if (!t) return;
-    // wait for the work the handle's calls enqueued (on whichever stream), not the whole device
-    if (t->done && hipEventSynchronize(t->done) != hipSuccess) {
-        (void)hipGetLastError();
-        t->unmarked = true;
-    }
-    if (t->unmarked && hipDeviceSynchronize() != hipSuccess) (void)hipGetLastError();
+    const bool idle = wait_done(t);
     Buf* bufs[] = {&t->particle_slab, &t->node_slab, &t->grad_slab, &t->sorted_counts, &t->step_temp, &t->lists, &t->list_len,
                    &t->small};
     for (Buf* b : bufs) release(t, *b);
     for (auto& e : t->ev)
         if (e) (void)hipEventDestroy(e);
-    if (t->host) give_host_pair({t->device, t->host, t->done});
+    for (int i = 1; i < kMarks; ++i)
+        if (t->marks[i].ev) (void)hipEventDestroy(t->marks[i].ev);
+    if (t->host) {
+        const HostPair hp{t->device, t->host, t->marks[0].ev};
+        // a mirror that a copy may still be on its way to serves no other handle
+        if (idle) give_host_pair(hp);
+        else free_host_pair(hp);
+    }
     delete t;
 }
 

@@ -1,0 +1,43 @@
+"""Handles used from several streams."""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("others", [1, 3, 4, 6])
+def test_free_waits_for_every_stream_the_handle_was_used_on(others):
+    """A force evaluation is held up on one stream by work of the caller's; the tree is
+    read on `others` more streams, which finish at once; freeing the handle waits for
+    the first all the same (its buffers and its host mirror go to the next handle),
+    and the next handle's diagnostics are its own."""
+    import paper_2412_01733_amd as tc
+    d = torch.device("cuda:0")
+    pos, m = (torch.from_numpy(a).to(d) for a in workloads.plummer(3000, 5, dtype=np.float32))
+    _, _, ref = tc.forces(pos, m, 0.5, 0.05)
+    want = ref.stats()["momentum"]
+    ref.free()
+    torch.cuda._sleep(1000)
+    slow, streams = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(others)]
+    torch.cuda.synchronize()
+    tree = tc.Tree()
+    with torch.cuda.stream(slow):
+        tree.build(pos, m).moments()
+        acc = torch.empty((3000, 3), device=d)
+        slow.synchronize()
+        torch.cuda._sleep(200_000_000)
+        tree.forces(0.5, 0.05, potential=False, out=(acc, None))
+        done = slow.record_event()
+    for s in streams:
+        with torch.cuda.stream(s):
+            tree.target_order()
+    assert not done.query()  # the case is what it says
+    tree.free()
+    assert done.query()
+    nxt = tc.forces(pos, 2 * m, 0.5, 0.05)[2]
+    got = nxt.stats()["momentum"]
+    torch.cuda.synchronize()
+    assert got == nxt.stats()["momentum"] and got == [4 * v for v in want]
