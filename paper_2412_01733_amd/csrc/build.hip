@@ -34,6 +34,13 @@ constexpr int kTreeWaves = kTreeThreads / 64;
 
 inline unsigned grid_for(int64_t n, int threads) { return (unsigned)((n + threads - 1) / threads); }
 
+LevelOffsets level_offsets(const uint32_t* host)
+{
+    LevelOffsets off;
+    for (int l = 0; l <= kLevels; ++l) off.off[l] = host[l];
+    return off;
+}
+
 // c_{s-1}, c_s and m_s of particle s.
 struct Span {
     int before, after, deepest;
@@ -85,6 +92,45 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_counts(const uint64_t* __
     }
 }
 
+// Of the block's particles by wavefront and level.
+struct BlockNodes {
+    uint64_t begins[kTreeWaves][kLevels];  // lanes whose particle begins a level-l node
+    uint32_t before[kTreeWaves][kLevels];  // number of the next level-l node at the wavefront's start
+};
+
+// Fills them in, and the span of this thread's particle s (none if s >= n).
+__device__ inline Span number_nodes(const uint64_t* __restrict__ k, int64_t n, const uint32_t* __restrict__ table,
+                                    const LevelOffsets& off, int64_t s, BlockNodes& nodes)
+{
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    Span span = {kMaxLevel, -1, 0};
+    if (s < n) span = particle_span(k, n, s);
+    uint64_t mine = 0;
+    for (int l = 0; l < kLevels; ++l) {
+        const uint64_t b = __ballot(span.before < l && l <= span.deepest);
+        if (lane == l) mine = b;
+    }
+    if (lane < kLevels) nodes.begins[w][lane] = mine;
+    __syncthreads();
+    if (threadIdx.x < kLevels) {
+        const int l = threadIdx.x;
+        uint32_t t = off.off[l] + table[(int64_t)l * gridDim.x + blockIdx.x];
+        for (int u = 0; u < kTreeWaves; ++u) {
+            nodes.before[u][l] = t;
+            t += (uint32_t)__popcll(nodes.begins[u][l]);
+        }
+    }
+    __syncthreads();
+    return span;
+}
+
+// Number of the level-l node that holds the particle of this lane.
+__device__ inline uint32_t node_number(const BlockNodes& nodes, int w, int lane, int l)
+{
+    const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;
+    return nodes.before[w][l] + (uint32_t)__popcll(nodes.begins[w][l] & upto) - 1u;
+}
+
 // Writes down the nodes (see above).  topo[b] = {first particle, first child,
 // meta, 0} comes from the node's first particle, ends[b] = {end, last child} from
 // its last one (not for one-particle leaves, whose walk record is complete here);
@@ -96,37 +142,14 @@ __global__ __launch_bounds__(kTreeThreads) void k_emit(const uint64_t* __restric
                                                        uint2* __restrict__ ends, WalkNode* __restrict__ wn,
                                                        uint32_t* __restrict__ leaf_of, uint32_t* __restrict__ status)
 {
-    __shared__ uint64_t begins[kTreeWaves][kLevels];  // lanes whose particle begins a level-l node
-    __shared__ uint32_t before[kTreeWaves][kLevels];  // number of the next level-l node at the wave's start
+    __shared__ BlockNodes nodes;
     const int64_t s = (int64_t)blockIdx.x * kTreeThreads + threadIdx.x;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (s == 0) *status = 0u;  // a build clears the walks' status word
-    Span span = {kMaxLevel, -1, 0};
-    uint64_t key = 0;
-    if (s < n) {
-        span = particle_span(k, n, s);
-        key = k[s];
-    }
-    uint64_t mine = 0;
-    for (int l = 0; l < kLevels; ++l) {
-        const uint64_t b = __ballot(span.before < l && l <= span.deepest);
-        if (lane == l) mine = b;
-    }
-    if (lane < kLevels) begins[w][lane] = mine;
-    __syncthreads();
-    if (threadIdx.x < kLevels) {
-        const int l = threadIdx.x;
-        uint32_t t = off.off[l] + table[(int64_t)l * gridDim.x + blockIdx.x];
-        for (int u = 0; u < kTreeWaves; ++u) {
-            before[u][l] = t;
-            t += (uint32_t)__popcll(begins[u][l]);
-        }
-    }
-    __syncthreads();
+    const Span span = number_nodes(k, n, table, off, s, nodes);
     if (s >= n) return;
-    // number of the level-l node that holds s
-    const uint64_t upto = lane == 63 ? ~0ull : (2ull << lane) - 1ull;
-    auto number = [&](int l) { return before[w][l] + (uint32_t)__popcll(begins[w][l] & upto) - 1u; };
+    const uint64_t key = k[s];
+    auto number = [&](int l) { return node_number(nodes, w, lane, l); };
     const int lowest = (span.before < span.after ? span.before : span.after) + 1;
     uint32_t below = 0;  // number of the node one level down
     for (int l = span.deepest; l >= lowest; --l) {
@@ -152,53 +175,37 @@ __global__ __launch_bounds__(kTreeThreads) void k_emit(const uint64_t* __restric
     if (lowest > span.deepest) leaf_of[s] = number(span.deepest);  // inside a leaf of coincident keys
 }
 
-// Pre-order number of the first node that begins at particle s (pre-order = by
-// (first, level), the order of the canonical export).
-__global__ __launch_bounds__(kTreeThreads) void k_preorder(const uint64_t* __restrict__ k, int64_t n,
-                                                           const uint32_t* __restrict__ table, uint32_t* __restrict__ pre)
+// The canonical export: the nodes in pre-order, i.e. by (first, level).  The nodes
+// that begin at one particle follow each other there, after as many as begin before
+// it at any level.  Reads the handle's tables only.
+__global__ __launch_bounds__(kTreeThreads) void k_export_nodes(const uint64_t* __restrict__ k, int64_t n,
+                                                               const uint32_t* __restrict__ table, LevelOffsets off,
+                                                               const uint2* __restrict__ ends, const WalkNode* __restrict__ wn,
+                                                               uint8_t* __restrict__ level, uint32_t* __restrict__ first,
+                                                               uint32_t* __restrict__ count, double* __restrict__ com,
+                                                               double* __restrict__ mass)
 {
-    __shared__ uint32_t wsum[kTreeWaves];
+    __shared__ BlockNodes nodes;
     const int64_t s = (int64_t)blockIdx.x * kTreeThreads + threadIdx.x;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    uint32_t c = 0;
-    if (s < n) {
-        const Span sp = particle_span(k, n, s);
-        c = sp.deepest > sp.before ? (uint32_t)(sp.deepest - sp.before) : 0u;
+    const Span span = number_nodes(k, n, table, off, s, nodes);
+    if (s >= n) return;
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t pre = 0;
+    for (int l = 0; l < kLevels; ++l) pre += nodes.before[w][l] - off.off[l] + (uint32_t)__popcll(nodes.begins[w][l] & below);
+    for (int l = span.before + 1; l <= span.deepest; ++l) {
+        const uint32_t b = node_number(nodes, w, lane, l);
+        const int64_t p = (int64_t)pre + (l - span.before - 1);
+        if (level) level[p] = (uint8_t)l;
+        if (first) first[p] = (uint32_t)s;
+        if (count) count[p] = l == span.deepest && span.after < l ? 1u : ends[b].x - (uint32_t)s;  // 1: a one-particle leaf
+        if (com) {
+            com[3 * p + 0] = wn[b].x;
+            com[3 * p + 1] = wn[b].y;
+            com[3 * p + 2] = wn[b].z;
+        }
+        if (mass) mass[p] = wn[b].m;
     }
-    uint32_t inc = c;
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t u = __shfl_up(inc, o, 64);
-        if (lane >= o) inc += u;
-    }
-    if (lane == 63) wsum[w] = inc;
-    __syncthreads();
-    uint32_t base = 0;
-    for (int l = 0; l < kLevels; ++l) base += table[(int64_t)l * gridDim.x + blockIdx.x];
-    for (int u = 0; u < w; ++u) base += wsum[u];
-    if (s < n) pre[s] = base + inc - c;
-}
-
-__global__ __launch_bounds__(256) void k_export_nodes(const uint64_t* __restrict__ k, int64_t n,
-                                                      const uint32_t* __restrict__ pre, const uint4* __restrict__ topo,
-                                                      const uint2* __restrict__ ends, const WalkNode* __restrict__ wn,
-                                                      int64_t nn, uint8_t* __restrict__ level, uint32_t* __restrict__ first,
-                                                      uint32_t* __restrict__ count, double* __restrict__ com,
-                                                      double* __restrict__ mass)
-{
-    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= nn) return;
-    const uint4 t = topo[b];
-    const int l = (int)meta_level(t.z);
-    const int64_t p = (int64_t)pre[t.x] + (l - 1 - (t.x > 0 ? shared_level(k[t.x - 1], k[t.x]) : -1));
-    if (level) level[p] = (uint8_t)l;
-    if (first) first[p] = t.x;
-    if (count) count[p] = meta_single(t.z) ? 1u : ends[b].x - t.x;
-    if (com) {
-        com[3 * p + 0] = wn[b].x;
-        com[3 * p + 1] = wn[b].y;
-        com[3 * p + 2] = wn[b].z;
-    }
-    if (mass) mass[p] = wn[b].m;
 }
 
 }  // namespace
@@ -215,17 +222,16 @@ void launch_tree_counts(const uint64_t* skeys, int64_t n, uint32_t* table, uint3
 void launch_emit(const uint64_t* skeys, int64_t n, const uint32_t* table, const uint32_t* level_off_host, const Particle* sp,
                  uint4* topo, uint2* ends, WalkNode* wn, uint32_t* leaf_of, uint32_t* status, hipStream_t s)
 {
-    LevelOffsets off;
-    for (int l = 0; l <= kLevels; ++l) off.off[l] = level_off_host[l];
-    k_emit<<<grid_for(n, kTreeThreads), kTreeThreads, 0, s>>>(skeys, n, table, off, sp, topo, ends, wn, leaf_of, status);
+    k_emit<<<grid_for(n, kTreeThreads), kTreeThreads, 0, s>>>(skeys, n, table, level_offsets(level_off_host), sp, topo, ends, wn,
+                                                              leaf_of, status);
 }
 
-void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table, uint32_t* pre, const uint4* topo,
-                         const uint2* ends, const WalkNode* wn, int64_t nn, uint8_t* level, uint32_t* first,
-                         uint32_t* count, double* com, double* mass, hipStream_t s)
+void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table, const uint32_t* level_off_host,
+                         const uint2* ends, const WalkNode* wn, uint8_t* level, uint32_t* first, uint32_t* count,
+                         double* com, double* mass, hipStream_t s)
 {
-    k_preorder<<<grid_for(n, kTreeThreads), kTreeThreads, 0, s>>>(skeys, n, table, pre);
-    k_export_nodes<<<grid_for(nn, 256), 256, 0, s>>>(skeys, n, pre, topo, ends, wn, nn, level, first, count, com, mass);
+    k_export_nodes<<<grid_for(n, kTreeThreads), kTreeThreads, 0, s>>>(skeys, n, table, level_offsets(level_off_host), ends, wn,
+                                                                      level, first, count, com, mass);
 }
 
 }  // namespace tc

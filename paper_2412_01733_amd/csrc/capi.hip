@@ -973,10 +973,8 @@ tc_status tc_tree_export(const tc_tree* t, uint64_t* keys, uint32_t* perm, uint8
     TC_TRY(cp(keys, t->skeys, n * 8));
     TC_TRY(cp(perm, t->perm, n * 4));
     if (level || first || count || com || mass) {
-        // the sort's spare key buffer holds the pre-order numbers meanwhile
-        uint32_t* pre = (uint32_t*)(t->skeys == P<uint64_t>(t->keys0) ? t->keys1.p : t->keys0.p);
-        launch_export_nodes(t->skeys, t->n, P<uint32_t>(t->tree_table), pre, P<uint4>(t->topo), P<uint2>(t->ends),
-                            P<WalkNode>(t->wn), t->nn, level, first, count, com, mass, s);
+        launch_export_nodes(t->skeys, t->n, P<uint32_t>(t->tree_table), t->host->level_off, P<uint2>(t->ends),
+                            P<WalkNode>(t->wn), level, first, count, com, mass, s);
         TC_TRY(check_launch("export"));
     }
     return mark_done(const_cast<tc_tree*>(t), s, TC_OK);

@@ -114,10 +114,10 @@ size_t tree_table_bytes(int64_t n);
 void launch_tree_counts(const uint64_t* skeys, int64_t n, uint32_t* table, uint32_t* totals, hipStream_t s);
 void launch_emit(const uint64_t* skeys, int64_t n, const uint32_t* table, const uint32_t* level_off_host, const Particle* sp,
                  uint4* topo, uint2* ends, WalkNode* wn, uint32_t* leaf_of, uint32_t* status, hipStream_t s);
-// Canonical export (pre-order); pre is scratch [n].  Any output may be null.
-void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table, uint32_t* pre, const uint4* topo,
-                         const uint2* ends, const WalkNode* wn, int64_t nn, uint8_t* level, uint32_t* first,
-                         uint32_t* count, double* com, double* mass, hipStream_t s);
+// Canonical export (pre-order); writes to the outputs only, any of which may be null.
+void launch_export_nodes(const uint64_t* skeys, int64_t n, const uint32_t* table, const uint32_t* level_off_host,
+                         const uint2* ends, const WalkNode* wn, uint8_t* level, uint32_t* first, uint32_t* count,
+                         double* com, double* mass, hipStream_t s);
 
 // moments.hip: the upward pass.  table as launch_tree_counts left it.
 void launch_moments(int64_t n, const uint32_t* table, const uint32_t* level_off_host, const uint4* topo, const uint2* ends, const uint64_t* skeys,

@@ -41,3 +41,49 @@ def test_free_waits_for_every_stream_the_handle_was_used_on(others):
     got = nxt.stats()["momentum"]
     torch.cuda.synchronize()
     assert got == nxt.stats()["momentum"] and got == [4 * v for v in want]
+
+
+@pytest.mark.parametrize("n", [700, 20000, 600001])
+def test_export_only_reads_the_handle(n):
+    """tc_tree_export takes a const handle: not a byte of the buffers it owns changes
+    (so exports on several streams do not meet), and exports that run at once agree."""
+    import paper_2412_01733_amd as tc
+    from paper_2412_01733_amd import _lib
+    d = torch.device("cuda:0")
+    pos, m = (torch.from_numpy(a).to(d) for a in workloads.plummer(n, 6, dtype=np.float32))
+    held = {}
+
+    def alloc(nbytes, stream, ctx):
+        t = torch.zeros(int(nbytes), dtype=torch.uint8, device=d)
+        held[t.data_ptr()] = t
+        return t.data_ptr()
+
+    def free(ptr, stream, ctx):
+        held.pop(int(ptr), None)
+
+    fa, ff = _lib.ALLOC_FN(alloc), _lib.FREE_FN(free)
+    tc.Tree()  # installs torch's allocator, if it is the first
+    lib = _lib.load()
+    try:
+        assert lib.tc_set_allocator(fa, ff, None) == _lib.TC_OK
+        tree = tc.Tree()
+        tree.build(pos, m).moments()
+        tree.forces(0.5, 0.05)
+        torch.cuda.synchronize()
+        before = {p: t.clone() for p, t in held.items()}
+        one = tree.export()
+        torch.cuda.synchronize()
+        assert before.keys() == held.keys()
+        for p, t in held.items():
+            assert torch.equal(before[p], t), int((before[p] != t).sum())
+        out = []
+        for s in (torch.cuda.Stream(), torch.cuda.Stream()):
+            with torch.cuda.stream(s):
+                out.append(tree.export())
+        torch.cuda.synchronize()
+        for e in out:
+            assert all(torch.equal(e[k], one[k]) for k in one)
+        tree.free()
+    finally:
+        assert lib.tc_set_allocator(_lib.ALLOC_FN(), _lib.FREE_FN(), None) == _lib.TC_OK
+        tc.treecode.bind_torch_allocator()
