@@ -34,6 +34,8 @@
 //   then, for i = 0, 1, 2 in turn: if X_i, flip[0] ^= 1, else exchange
 //   (perm, flip) entries 0 and i; parity ^= X_0^X_1^X_2.
 // State word: perm[a] in bits 2a..2a+1, flip[a] in bit 6 + a, parity in bit 9.
+#include <cstddef>
+
 #include "tc_internal.h"
 
 namespace tc {
@@ -75,9 +77,9 @@ constexpr uint32_t hilbert_step(uint32_t st, uint32_t d, uint32_t* child_state)
 // (the root is 0), as a table: next[state][octant] and digits[state], 4 bits an
 // octant.  A step down the key is one LDS read instead of ~40 instructions.
 struct HilbertTable {
-    int count;
-    uint8_t next[128][8];
+    alignas(8) uint8_t next[128][8];
     uint32_t digits[128];
+    int count;
 };
 
 constexpr HilbertTable make_hilbert_table()
@@ -112,6 +114,8 @@ __global__ __launch_bounds__(256) void k_order_children(int64_t nn, const uint64
 {
     __shared__ uint2 next[kHilbertStates];  // a byte an octant
     __shared__ uint32_t digits[kHilbertStates];
+    static_assert(alignof(HilbertTable) % alignof(uint2) == 0 && offsetof(HilbertTable, next) % alignof(uint2) == 0 &&
+                      sizeof(kHilbert.next[0]) == sizeof(uint2), "a row is read as a uint2");
     for (int i = threadIdx.x; i < kHilbertStates; i += blockDim.x) {
         next[i] = *reinterpret_cast<const uint2*>(kHilbert.next[i]);
         digits[i] = kHilbert.digits[i];
