@@ -11,7 +11,7 @@
 #include <mutex>
 #include <string>
 #include <thread>
-#include <vector>
+#include <type_traits>
 
 #include "tc_internal.h"
 
@@ -263,18 +263,25 @@ struct HostPair {
     HostMirror* host;
     hipEvent_t done;
 };
-constexpr size_t kHostPool = 8;
+constexpr int kHostPool = 8;
 std::mutex g_host_mu;
-std::vector<HostPair> g_host_pool;
+struct HostPool {
+    HostPair pair[kHostPool];
+    int count;
+} g_host_pool;
+// Giving a pair back must not throw (tc_tree_free is a C entry), and a handle may be
+// freed while the process ends, after static objects with destructors are gone.
+static_assert(std::is_trivially_destructible<HostPool>::value && std::is_nothrow_copy_assignable<HostPair>::value,
+              "no allocation, no destructor");
 
 tc_status take_host_pair(int dev, HostPair* out)
 {
     {
         std::lock_guard<std::mutex> lk(g_host_mu);
-        for (size_t i = 0; i < g_host_pool.size(); ++i) {
-            if (g_host_pool[i].device != dev) continue;
-            *out = g_host_pool[i];
-            g_host_pool.erase(g_host_pool.begin() + (ptrdiff_t)i);
+        for (int i = 0; i < g_host_pool.count; ++i) {
+            if (g_host_pool.pair[i].device != dev) continue;
+            *out = g_host_pool.pair[i];
+            g_host_pool.pair[i] = g_host_pool.pair[--g_host_pool.count];
             return TC_OK;
         }
     }
@@ -301,8 +308,8 @@ void give_host_pair(const HostPair& p)
 {
     {
         std::lock_guard<std::mutex> lk(g_host_mu);
-        if (g_host_pool.size() < kHostPool) {
-            g_host_pool.push_back(p);
+        if (g_host_pool.count < kHostPool) {
+            g_host_pool.pair[g_host_pool.count++] = p;
             return;
         }
     }

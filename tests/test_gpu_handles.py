@@ -87,3 +87,19 @@ def test_export_only_reads_the_handle(n):
     finally:
         assert lib.tc_set_allocator(_lib.ALLOC_FN(), _lib.FREE_FN(), None) == _lib.TC_OK
         tc.treecode.bind_torch_allocator()
+
+
+def test_more_handles_than_the_pool_keeps():
+    """Twelve handles at once (the pool of host mirrors keeps eight), freed out of
+    order and made anew, each with its own diagnostics."""
+    import paper_2412_01733_amd as tc
+    d = torch.device("cuda:0")
+    sets = [[torch.from_numpy(a).to(d) for a in workloads.plummer(500 + 7 * i, i, dtype=np.float32)] for i in range(12)]
+    want = None
+    for _ in range(3):
+        trees = [tc.forces(p, m, 0.5, 0.05)[2] for p, m in sets]
+        got = [t.stats()["momentum"] for t in trees]
+        assert want is None or got == want
+        want = got
+        for i in (3, 0, 11, 5, 1, 2, 4, 10, 9, 8, 7, 6):
+            trees[i].free()
