@@ -20,15 +20,27 @@ def test_free_waits_for_every_stream_the_handle_was_used_on(others):
     _, _, ref = tc.forces(pos, m, 0.5, 0.05)
     want = ref.stats()["momentum"]
     ref.free()
-    torch.cuda._sleep(1000)
     slow, streams = torch.cuda.Stream(), [torch.cuda.Stream() for _ in range(others)]
+    # everything once beforehand, so that first calls do not take the time of the wait below
+    for s in [slow] + streams:
+        with torch.cuda.stream(s):
+            t = tc.Tree().build(pos, m).moments()
+            t.forces(0.5, 0.05)
+            t.target_order()
+            t.free()
+    begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    torch.cuda._sleep(1000)
+    begin.record()
+    torch.cuda._sleep(10_000_000)
+    end.record()
     torch.cuda.synchronize()
+    half_a_second = int(10_000_000 * 500.0 / begin.elapsed_time(end))
     tree = tc.Tree()
     with torch.cuda.stream(slow):
         tree.build(pos, m).moments()
         acc = torch.empty((3000, 3), device=d)
         slow.synchronize()
-        torch.cuda._sleep(200_000_000)
+        torch.cuda._sleep(half_a_second)
         tree.forces(0.5, 0.05, potential=False, out=(acc, None))
         done = slow.record_event()
     for s in streams:
