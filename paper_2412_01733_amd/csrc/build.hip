@@ -41,17 +41,18 @@ LevelOffsets level_offsets(const uint32_t* host)
     return off;
 }
 
-// c_{s-1}, c_s and m_s of particle s.
+// c_{s-1}, c_s and m_s of particle s, and its key.
 struct Span {
     int before, after, deepest;
+    uint64_t key;
 };
 
 __device__ inline Span particle_span(const uint64_t* __restrict__ k, int64_t n, int64_t s)
 {
     Span r;
-    const uint64_t key = k[s];
-    r.before = s > 0 ? shared_level(k[s - 1], key) : -1;
-    r.after = s + 1 < n ? shared_level(key, k[s + 1]) : -1;
+    r.key = k[s];
+    r.before = s > 0 ? shared_level(k[s - 1], r.key) : -1;
+    r.after = s + 1 < n ? shared_level(r.key, k[s + 1]) : -1;
     const int m = (r.before > r.after ? r.before : r.after) + 1;
     r.deepest = m < kMaxLevel ? m : kMaxLevel;
     return r;
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_tree_counts(const uint64_t* __
     __shared__ uint32_t h[kTreeWaves][kTreeRows];
     const int64_t s = (int64_t)blockIdx.x * kTreeThreads + threadIdx.x;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    Span sp = {kMaxLevel, -1, 0};  // begins nothing
+    Span sp = {kMaxLevel, -1, 0, 0};  // begins nothing
     if (s < n) sp = particle_span(k, n, s);
     uint32_t acc = 0;  // lane l keeps row l
     for (int l = 0; l < kLevels; ++l) {
@@ -103,7 +104,7 @@ __device__ inline Span number_nodes(const uint64_t* __restrict__ k, int64_t n, c
                                     const LevelOffsets& off, int64_t s, BlockNodes& nodes)
 {
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    Span span = {kMaxLevel, -1, 0};
+    Span span = {kMaxLevel, -1, 0, 0};
     if (s < n) span = particle_span(k, n, s);
     uint64_t mine = 0;
     for (int l = 0; l < kLevels; ++l) {
@@ -148,7 +149,6 @@ __global__ __launch_bounds__(kTreeThreads) void k_emit(const uint64_t* __restric
     if (s == 0) *status = 0u;  // a build clears the walks' status word
     const Span span = number_nodes(k, n, table, off, s, nodes);
     if (s >= n) return;
-    const uint64_t key = k[s];
     auto number = [&](int l) { return node_number(nodes, w, lane, l); };
     const int lowest = (span.before < span.after ? span.before : span.after) + 1;
     uint32_t below = 0;  // number of the node one level down
@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_emit(const uint64_t* __restric
         if (leaf) leaf_of[s] = b;
         const bool single = leaf && span.before < l && span.after < l;
         if (span.before < l) {
-            const uint32_t oct = l > 0 ? (uint32_t)((key >> (3 * (kMaxLevel - l))) & 7u) : 0u;
+            const uint32_t oct = l > 0 ? (uint32_t)((span.key >> (3 * (kMaxLevel - l))) & 7u) : 0u;
             const uint32_t meta = ((uint32_t)l << 8) | (single ? (1u << 13) | (1u << 17) : 0u) | (leaf ? 1u << 16 : 0u) | (oct << 18);
             topo[b] = make_uint4((uint32_t)s, leaf ? 0u : below, meta, 0u);
             if (single) {
