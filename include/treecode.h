@@ -129,8 +129,9 @@ tc_status tc_forces(tc_tree* tree, double theta, double eps, double G, tc_walk m
  * writes g_pos = dL/dx [n,3] and g_mass = dL/dm [n] (either may be NULL), all
  * in the caller's order and in the dtype of the last walk's outputs.
  * Each wavefront of 64 targets replays the records the last tc_forces stored
- * (TC_STORE_LISTS) or, without them, re-walks the tree with the same
- * decisions and arithmetic; the two agree to rounding (summation order).
+ * (TC_STORE_LISTS); without them the tree is walked again with the same
+ * decisions and terms, grouped by n.  The two agree to rounding (summation
+ * order).
  * Errors: TC_ERR_INVALID, TC_ERR_STATE (no tc_forces since the last build),
  * TC_ERR_NOMEM, TC_ERR_DEVICE. */
 tc_status tc_forces_backward(tc_tree* tree, const void* g_acc, const void* g_pot,
@@ -246,8 +247,9 @@ tc_status tc_tree_export(const tc_tree* tree, uint64_t* keys, uint32_t* perm, ui
                          void* stream);
 
 /* The walk's target order, set by tc_moments: order u32[n] (device), the
- * sorted positions of the particles along the Hilbert curve; wavefront w of
- * every walk serves the targets order[64 w .. 64 w + 63].  It fixes only how
+ * sorted positions of the particles along the Hilbert curve; a wavefront, or a
+ * team of them, serves 64, 16 or 8 targets that follow each other in it (by
+ * n; 64 when interactions are counted or lists stored).  It fixes only how
  * targets are grouped, never a result (each target's interaction set is its
  * own, section 2).  Provided for tests and diagnostics.
  * Errors: TC_ERR_INVALID, TC_ERR_STATE (no tc_moments since the last build). */

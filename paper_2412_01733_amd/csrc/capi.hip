@@ -626,11 +626,13 @@ tc_status backward_impl(tc_tree* t, const void* g_acc, const void* g_pot, void* 
     stage_begin(t, kStBwdWalk, s);
     launch_fill_f64_zero(a.node_grad, nn * 4, s);
     if (multi) launch_fill_f64_zero(a.part_grad, n * 4, s);
-    // FP32 sums handed back as the gradients of FP64 particles keep the order and the
-    // partial sums of the single-group walk (walk.hip, which also replays lists).
-    // Another order moves them by the FP32 rounding, 1e-7, which is much for an FP64
-    // result; the faster walks are for gradients of the walk's own precision (at 21708
-    // particles, theta = 0.3, a pass takes 3.1 ms with this walk, 0.8 ms with those).
+    // F32C gradients of FP64 particles come from the single-group walk (walk.hip, which
+    // also replays lists).  It is no more accurate than the others: median error against
+    // the FP64 adjoint at 21708 particles, theta = 0.5, dL/dx 2.94e-7 here and 2.93e-7
+    // there, dL/dm 2.06e-7 and 2.06e-7 (2.62e-7 / 2.60e-7, 1.96e-7 / 1.95e-7 at 250000).
+    // Nor is it faster: 1095 and 192 us a backward pass there, 1757 and 1014 at 250000.
+    // It is kept because TreeForces hands these gradients back as FP64, and another
+    // order of the FP32 sums would change them by 1e-7.
     const bool single_groups = t->lists_stored || (t->dtype == TC_F64 && t->last_mode == TC_WALK_F32C);
     const int targets = single_groups ? 64 : adjoint_targets(n);
     if (targets < 64) launch_walk_split_adjoint(a, t->last_mode, s);

@@ -127,7 +127,7 @@ void launch_moments(int64_t n, const uint32_t* table, const uint32_t* level_off_
 struct WalkArgs {
     const WalkNode* nodes;
     const Particle* sp;     // particles in key order
-    const uint32_t* order;  // [n] targets by wavefront: wavefront w takes order[64 w .. 64 w + 63]
+    const uint32_t* order;  // [n] targets: a wavefront (or team) takes 64, 16 or 8 that follow each other
     const uint32_t* perm;
     int64_t n;
     double eps2;
@@ -137,7 +137,7 @@ struct WalkArgs {
     void* acc;              // caller order, FP32 (F32C) or FP64 (F64)
     void* pot;              // may be NULL
     uint32_t* counts;       // sorted order (counting walk only)
-    double* diag;           // [waves, 4] partials of sum m a, sum m |a|
+    double* diag;           // [wavefronts or teams, 4] partials of sum m a, sum m |a|
     uint32_t* status;       // bit 0: stack overflow (never expected)
     unsigned long long* visits;  // counting walk: [kNumVisitCounters], see tc_stats (node_visits ... max_stack)
     // adjoint walk only

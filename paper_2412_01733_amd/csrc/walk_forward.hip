@@ -64,11 +64,13 @@ constexpr uint32_t kXcdRun = 64;  // consecutive blocks one XCD takes at a time
 // by being safe, and the first entry does (142).  A push beyond the stack
 // therefore cannot happen; it would be refused and flagged (status bit 0).
 // Shapes, measured at Plummer 1e7, theta = 0.5: sibling groups a step takes at
-// most, stack entries, wavefronts per SIMD that the registers and LDS allow, and
-// how many accepted children a sparse group must exceed to be transposed.
-//   F32C (ms): 5 groups 12.43, 6 groups 12.11, 7 groups 12.39; 8 wavefronts (two
-//   registers spilled) 12.12; never transposed 12.67; groups of up to 16 lanes
-//   transposed as well (4 children x 16 targets, twice) 12.83.
+// most, stack entries, wavefronts per SIMD that the compiler is asked for (F32C
+// compiles to 56 registers and 18.6 KB of LDS a block, which 8 share, FP64 to 68 and
+// 22.7 KB, 7), and how many accepted children a sparse group must exceed to be
+// transposed.
+//   F32C (ms): 5 groups 12.43, 6 groups 12.11, 7 groups 12.39; never transposed
+//   12.67; groups of up to 16 lanes transposed as well (4 children x 16 targets,
+//   twice) 12.83.
 //   FP64 (ms): 6 groups 22.55, 7 groups 22.26, 8 groups 21.97; never transposed 25.4.
 // A team: the four wavefronts of a block serve the same 64 targets, share one
 // stack and take a quarter of each step's groups each, so that a walk is a
@@ -425,7 +427,8 @@ void k_walk_fwd(WalkArgs a)
             }
         }
         team_sync<TEAM>();  // the next step restages the slots and rereads the stack
-        // a step adds up to 48 terms per lane to the plain partial sums.  F32C: folded every step the
+        // a step adds up to 8 terms a group and lane to the plain partial sums (F32C 48, folded every
+        // step; FP64 64, every second), and the particles of opened leaves.  F32C: folded every step the
         // median error of acc against FP64 is 5.1e-8 at 1e6 (6.8e-8 every second step), at the same speed
         if (++since_fold == (F64 ? 2 : 1) || sp == 0) {
             since_fold = 0;

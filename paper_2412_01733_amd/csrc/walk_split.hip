@@ -340,7 +340,8 @@ __global__ __launch_bounds__(64 * block_waves(TEAM)) void k_walk_split(WalkArgs 
             }
         }
         team_sync<TEAM>();
-        // at most 64 / S terms a lane and step go into the plain sums
+        // F32C: a step adds up to 64 / S + 1 terms a lane to the plain sums (lists A and M are
+        // padded apart), so up to 2 (64 / S + 1) between folds, and the particles of opened leaves
         if (++since_fold == 2 || sp == 0) {
             since_fold = 0;
             if constexpr (F64) {
